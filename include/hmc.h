@@ -232,10 +232,13 @@ int hmc_set_state(hmc_lattice* L, const void* host_buf, size_t bytes);
  * over z_chunk planes.  sites_per_thread in {1, 2, 4}; z_chunk in
  * [1, 1024].  The spins produced do not depend on the shape (random
  * numbers are keyed by site); reduction orders, and so the last bits of
- * the observables, do.  Default: 2 sites per thread (1 where the LDS
- * window of 512 sites would not fit) and z_chunk 16; lattices whose spins
- * exceed 256 MiB (the march that loads two planes ahead) take 8 at FP32
- * and 32 at FP64.
+ * the observables, do.  Default: for spins up to 256 MiB the shortest
+ * z_chunk (at most 16) whose work-groups run in one round of the device, with
+ * 1 site per thread where that leaves short slabs, else 2; above 256 MiB (the
+ * march that loads two planes ahead) 2 sites per thread with z_chunk 8 at
+ * FP32 and 32 at FP64 (16 with bond masks).  hmc_get_launch gives the shape
+ * hmc_sweep uses.  In a batch, a lattice whose shape was not set takes a
+ * default of its own: (1, 4), and (2, 8) for FP64 lattices above 64^3 spins.
  * Errors: HMC_EINVAL. */
 int hmc_set_launch(hmc_lattice* L, int32_t sites_per_thread, int32_t z_chunk);
 int hmc_get_launch(const hmc_lattice* L, int32_t* sites_per_thread, int32_t* z_chunk);
@@ -342,7 +345,8 @@ size_t hmc_batch_workspace_bytes(int32_t count);
 
 /* Builds a batch over lattices[0 .. count-1] (distinct handles, one
  * precision, one stream).  The launch shape of each lattice is the one set
- * by hmc_set_launch (a later change is picked up by the next batch call).
+ * by hmc_set_launch (a later change is picked up by the next batch call), or
+ * the default of batches named there.
  * Lattices with bond masks are not accepted (they are swept alone).
  * Errors: HMC_EINVAL (null, duplicate, mixed precision or stream, bond
  * masks), HMC_ENOMEM (workspace too small or misaligned), HMC_EHIP. */

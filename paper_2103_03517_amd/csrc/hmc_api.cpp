@@ -318,18 +318,8 @@ int hmc_init_lattice(const hmc_params* p, void* dev_ws, size_t ws_bytes, void* h
         L->c1d[th] = 2.0 * s * s;
         L->c1f[th] = (float)L->c1d[th];
     }
-    // default launch shape: 512 in-plane sites per work-group, narrowed to
-    // 256 sites when the LDS window would exceed its budget; 16 planes while
-    // the spins fit the last-level cache.  Spins that stream from HBM (the
-    // depth-two march) take 8 planes at FP32: shorter slabs give more
-    // work-groups to spread over the chip (measured on MI355X at 384^3 and
-    // 464^3 FP32: 2.9 % and 1.9 % faster passes), and the finalize folds the
-    // extra records in parallel.  At FP64 they take 32: fewer slab ends to
-    // re-read (measured on MI355X: 256^3 63.9-64.3 against 62.8-63.0 G
-    // updates/s with 16 planes and 60.4 with 8; 384^3 61.0-61.4 against
-    // 60.3-60.7).
-    if (hmc::pass_lds_bytes(p->precision, d.hx, L->spt) > hmc::kMaxLds) L->spt = 1;
-    if (hmc::pass_deep(d)) L->zc = p->precision == 32 ? 8 : 32;
+    hmc::default_shape(d, &L->spt, &L->zc);
+    hmc::default_batch_shape(d, &L->batch_spt, &L->batch_zc);
     memset(&L->init_state, 0, sizeof(L->init_state));
     L->init_state.theta = p->theta0_deg;
 
@@ -733,8 +723,8 @@ int hmc_set_launch(hmc_lattice* L, int32_t sites_per_thread, int32_t z_chunk)
     if (z_chunk < 1 || z_chunk > 1024) return fail(L, HMC_EINVAL, "z_chunk must be in [1, 1024]");
     if (hmc::pass_lds_bytes(L->d.precision, L->d.hx, sites_per_thread) > hmc::kMaxLds)
         return fail(L, HMC_EINVAL, "launch shape needs more than 64 KiB of LDS");
-    L->spt = sites_per_thread;
-    L->zc = z_chunk;
+    L->spt = L->batch_spt = sites_per_thread;
+    L->zc = L->batch_zc = z_chunk;
     return HMC_OK;
 }
 

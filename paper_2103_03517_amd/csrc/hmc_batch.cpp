@@ -158,7 +158,7 @@ int refresh_table(hmc_batch* B)
     const size_t n = B->lat.size();
     bool same = B->table_valid;
     for (size_t i = 0; i < n && same; ++i)
-        same = B->shape[i] == std::make_pair(B->lat[i]->spt, B->lat[i]->zc);
+        same = B->shape[i] == std::make_pair(B->lat[i]->batch_spt, B->lat[i]->batch_zc);
     if (same) return HMC_OK;
 
     hipError_t e = staging_wait(B);
@@ -167,8 +167,8 @@ int refresh_table(hmc_batch* B)
     uint32_t* idx = reinterpret_cast<uint32_t*>(B->staging + B->lay.off_idx);
     for (size_t i = 0; i < n; ++i) {
         hmc_lattice* L = B->lat[i];
-        B->shape[i] = {L->spt, L->zc};
-        hmc::batch_fill_entry(tab + i * B->lay.entry, L->d, L->spt, L->zc);
+        B->shape[i] = {L->batch_spt, L->batch_zc};
+        hmc::batch_fill_entry(tab + i * B->lay.entry, L->d, L->batch_spt, L->batch_zc);
     }
     // chunks of consecutive lattices: k = ceil(total / chunk_bytes) chunks
     // of about equal bytes of spins (lattice i goes to the chunk that holds
@@ -199,7 +199,7 @@ int refresh_table(hmc_batch* B)
     for (auto& c : B->chunks) {
         std::vector<std::vector<uint32_t>> members(hmc::kBatchGroups);
         for (uint32_t i = c.first; i < c.first + c.count; ++i)
-            members[hmc::batch_group(B->lat[i]->d, B->lat[i]->spt)].push_back(i);
+            members[hmc::batch_group(B->lat[i]->d, B->lat[i]->batch_spt)].push_back(i);
         for (int g = 0; g < hmc::kBatchGroups; ++g) {
             const auto& m = members[g];
             if (m.empty()) continue;
@@ -218,8 +218,8 @@ int refresh_table(hmc_batch* B)
                 const hmc_lattice* L = B->lat[m[j]];
                 start[j] = (uint32_t)acc;
                 ent[j] = m[j];
-                acc += (uint64_t)hmc::pass_blocks(L->d, L->spt, L->zc);
-                lds = std::max(lds, hmc::pass_lds_bytes(B->precision, L->d.hx, L->spt));
+                acc += (uint64_t)hmc::pass_blocks(L->d, L->batch_spt, L->batch_zc);
+                lds = std::max(lds, hmc::pass_lds_bytes(B->precision, L->d.hx, L->batch_spt));
             }
             if (acc > 0x7FFFFFFFull)
                 return bfail(B, HMC_EINVAL, "batch needs more than 2^31 work-groups per launch");
@@ -552,7 +552,7 @@ int hmc_batch_tune(hmc_batch* B, const double* T, int32_t trial_sweeps)
     for (const auto& members : order) {
         if (st != HMC_OK) break;
         const hmc_lattice* L0 = B->lat[members[0]];
-        std::pair<int, int> best = {L0->spt, L0->zc};
+        std::pair<int, int> best = {L0->batch_spt, L0->batch_zc};
         float best_ms = 0.f;
         st = time_chunked(&best_ms);
         for (int spt : {1, 2, 4}) {
@@ -560,8 +560,8 @@ int hmc_batch_tune(hmc_batch* B, const double* T, int32_t trial_sweeps)
             for (int zc = 2; zc <= 64 && zc <= L0->d.nz && st == HMC_OK; zc *= 2) {
                 if (std::make_pair(spt, zc) == best) continue;
                 for (size_t i : members) {
-                    B->lat[i]->spt = spt;
-                    B->lat[i]->zc = zc;
+                    B->lat[i]->batch_spt = spt;
+                    B->lat[i]->batch_zc = zc;
                 }
                 float ms = 0.f;
                 st = time_chunked(&ms);
@@ -572,8 +572,8 @@ int hmc_batch_tune(hmc_batch* B, const double* T, int32_t trial_sweeps)
             }
         }
         for (size_t i : members) {
-            B->lat[i]->spt = best.first;
-            B->lat[i]->zc = best.second;
+            B->lat[i]->batch_spt = B->lat[i]->spt = best.first;
+            B->lat[i]->batch_zc = B->lat[i]->zc = best.second;
         }
     }
     // and the chunk size again with the final shapes

@@ -61,7 +61,8 @@ struct hmc_lattice {
     hmc_params p;
     hipStream_t stream;
     hmc::Layout lay;
-    int spt = 2, zc = 16;
+    int spt = 2, zc = 16;             // launch shape of the lattice's own sweeps
+    int batch_spt = 2, batch_zc = 16; // and in a batch; hmc_set_launch sets both
     bool m_valid = false;
     char err[256] = {0};
     double c1d[181];

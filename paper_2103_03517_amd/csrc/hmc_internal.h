@@ -122,6 +122,10 @@ hipError_t launch_finalize(const DevLattice& d, int64_t red_blocks, int64_t blac
 int64_t pass_blocks(const DevLattice& d, int spt, int zc);
 // Dynamic LDS bytes of the standard pass for a launch shape.
 size_t pass_lds_bytes(int precision, int hx, int spt);
+// Launch shape (sites per thread, z chunk) of the standard pass where none was
+// set: of a lattice swept alone, and of one swept in a batch.
+void default_shape(const DevLattice& d, int* spt, int* zc);
+void default_batch_shape(const DevLattice& d, int* spt, int* zc);
 // Largest partial count any launch can need.
 int64_t max_blocks_for(int32_t nx, int32_t ny, int32_t nz);
 // Groups of 1024 records the finalize folds for n work-group records; the

@@ -590,6 +590,56 @@ int64_t pass_blocks(const DevLattice& d, int spt, int zc)
     return (int64_t)cdiv((uint64_t)d.P, (uint64_t)kThreads * spt) * (int64_t)cdiv((uint64_t)d.nz, (uint64_t)zc);
 }
 
+// The launch shape where none was set.  A step of the march is bound by the
+// latency of its loads (about 1.2 us a plane), so a lattice that the last-level
+// cache holds takes the shortest slabs whose work-groups still run in one
+// round: kRoundBlocks of them (four of 256 threads to a compute unit at FP32,
+// two at FP64, whose march holds twice the registers).  One site per thread
+// while that leaves short slabs, else two, which share a slab's fixed cost.
+// Measured on MI355X, sampled sweeps, against (2, 16): 32^3 FP32 (1, 1) 13.3
+// us for 47.8, 128^3 (1, 4) 27.8 for 51.3, 192^3 (2, 8) 60.7 for 72.6, 256^3
+// (2, 16) 110.6 and every other shape above 116; FP64 32^3 (1, 1) 15.3 for
+// 72.6, 128^3 (1, 8) 47.3 for 82.5.  Spins that stream from HBM (the
+// depth-two march) take 8 planes at FP32 and 32 at FP64: shorter slabs spread
+// better (384^3 FP32 2.9 %, 464^3 1.9 % faster than 16 planes), longer ones
+// re-read fewer slab ends (256^3 FP64 63.9 G updates/s for 62.8 with 16).
+void default_shape(const DevLattice& d, int* spt, int* zc)
+{
+    const bool wide = pass_lds_bytes(d.precision, d.hx, 2) > kMaxLds;   // no room for two sites per thread
+    if (pass_deep(d) || (uint64_t)d.N * 3ull * (uint64_t)(d.precision / 8) > kDeepMarchBytes) {
+        *spt = wide ? 1 : 2;
+        *zc = d.mask ? 16 : (d.precision == 32 ? 8 : 32);
+        return;
+    }
+    constexpr int kRoundBlocks[2] = {1024, 512}, kShortSlab[2] = {4, 8};   // FP32, FP64
+    const int p = d.precision == 32 ? 0 : 1;
+    for (int s = 1; s <= 2; ++s) {
+        const int nqb = (int)cdiv((uint64_t)d.P, (uint64_t)kThreads * s);
+        const int slabs = kRoundBlocks[p] / nqb;                         // as many as one round holds
+        const int planes = slabs > 0 ? (int)cdiv((uint64_t)d.nz, (uint64_t)slabs) : d.nz;
+        *spt = s;
+        *zc = planes < 16 ? planes : 16;
+        if (*zc <= kShortSlab[p] || (s == 1 && wide)) return;
+    }
+}
+
+// In a batch the other lattices fill the chip, so the slabs are as long as
+// re-reading their ends asks for, whatever the batch holds (a lattice's
+// result must not depend on its company).  Measured on MI355X, us per sampled
+// batch sweep: FP32, 24 lattices of 48^3 to 128^3: (1, 4) 148, (1, 8) 147, (1, 2)
+// 174, (2, 16) 182; 8 of 32^3 to 64^3: (1, 4) 22.5, (1, 8) 27.9, (2, 16) 62.  FP64, the same:
+// (2, 8) 387, (1, 8) 421, (1, 4) 466; 8 small ones: (1, 4) 30, (1, 8) 35, (2, 8) 51.
+void default_batch_shape(const DevLattice& d, int* spt, int* zc)
+{
+    if ((uint64_t)d.N * 3ull * (uint64_t)(d.precision / 8) > kDeepMarchBytes) {
+        default_shape(d, spt, zc);
+        return;
+    }
+    const bool two = d.precision == 64 && d.N > (int64_t)64 * 64 * 64 && pass_lds_bytes(64, d.hx, 2) <= kMaxLds;
+    *spt = two ? 2 : 1;
+    *zc = two ? 8 : 4;
+}
+
 // Colour-split bond masks from masks in site order: site i = 2k + p of row
 // (y, z) has colour c = (x + y + z) & 1 and colour index k.
 __global__ __launch_bounds__(kThreads) void split_masks_kernel(const uint8_t* src, uint8_t* dst, uint32_t Nc,

@@ -1,0 +1,54 @@
+"""Default launch shapes: the spins are those of any other shape, the shapes
+stay within one round of the device, and a lattice of a batch whose shape was
+not set ends where it ends alone with the batch's default shape."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# around the lines of the rule: one slab per plane, 256-site blocks just full
+# and just not, two sites per thread, the 16-plane cap, an odd open film, nx = 1024
+SHAPES = [(2, 2, 2), (16, 16, 16), (34, 30, 18), (64, 64, 64), (66, 64, 64), (128, 128, 20), (320, 320, 12),
+          (1024, 256, 6), (1024, 1024, 4)]
+
+
+@pytest.fixture(scope="module")
+def H():
+    import torch
+    import paper_2103_03517_amd as H
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    H.lib()
+    return H
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_default_shape_gives_the_same_spins(H, shape, precision):
+    kw = dict(precision=precision, J=1.0, Ku=0.02, Kc=-0.03, h=(0.01, 0.0, 0.02), seed=11, init="random")
+    g, ref = H.Lattice(*shape, **kw), H.Lattice(*shape, **kw)
+    spt, zc = g.get_launch()
+    columns = -(-(shape[0] // 2 * shape[1]) // (256 * spt))
+    slabs = -(-shape[2] // zc)
+    assert zc <= 16 and (columns * slabs <= (1024 if precision == 32 else 512) or zc == min(16, shape[2]))
+    ref.set_launch(1, 3)
+    for lat in (g, ref):
+        lat.sweep(0.9, 3, sample=True)
+        lat.sweep(0.9, 2)
+    assert np.array_equal(g.spins(), ref.spins())
+    a, b = g.observables(), ref.observables()
+    assert a["theta_deg"] == b["theta_deg"] and a["accepted_last"] == b["accepted_last"]
+    assert np.allclose(a["mean_m"], b["mean_m"], rtol=0, atol=1e-6 if precision == 32 else 1e-13)
+
+
+@pytest.mark.parametrize("shape,precision,default", [((16, 16, 16), 32, (1, 4)), ((64, 64, 64), 64, (1, 4)),
+                                                     ((66, 64, 64), 64, (2, 8)), ((66, 64, 64), 32, (1, 4))])
+def test_batch_default_shape(H, shape, precision, default):
+    kw = dict(precision=precision, J=1.0, Ku=0.02, seed=5, init="random")
+    alone, inb, other = H.Lattice(*shape, **kw), H.Lattice(*shape, **kw), H.Lattice(8, 8, 8, **dict(kw, instance=3))
+    alone.set_launch(*default)
+    B = H.Batch([other, inb])
+    for n, smp in [(2, False), (3, True)]:
+        B.sweep(0.8, n, sample=smp)
+        alone.sweep(0.8, n, sample=smp)
+    assert alone.get_state() == inb.get_state()
+    B.close()
