@@ -62,7 +62,7 @@ BatchLayout batch_layout(int32_t count, int precision)
     off += align_up((size_t)count * sizeof(double), kAlign);
     b.off_fin = off;
     off += align_up((size_t)count * sizeof(int32_t), kAlign);
-    b.total = off;
+    b.total = std::max(off, align_up((size_t)count * sizeof(hmc::DevState), kAlign));   // staging of the observables
     return b;
 }
 
@@ -85,6 +85,9 @@ struct hmc_batch {
     };
     std::vector<Chunk> chunks;
     size_t chunk_bytes = 0;
+    // the measurement of all lattices: its work-group offsets (device) and total
+    const uint32_t* meas_start = nullptr;
+    uint32_t meas_blocks = 0;
     // pinned staging of the uploads: a ring of kRing buffers, each reused
     // once the copy last made from it has run, so that the host can prepare
     // uploads while earlier work is still queued; staging and upload_done
@@ -230,6 +233,15 @@ int refresh_table(hmc_batch* B)
             c.launches.push_back(bl);
         }
     }
+    // the work-group offsets of the measurement (n + 1 words more)
+    uint64_t macc = 0;
+    for (size_t i = 0; i <= n; ++i) {
+        idx[cursor + i] = (uint32_t)macc;
+        if (i < n) macc += (uint64_t)hmc::measure_blocks(B->lat[i]->d);
+    }
+    if (macc > 0x7FFFFFFFull) return bfail(B, HMC_EINVAL, "batch needs more than 2^31 work-groups per launch");
+    B->meas_start = dev_idx + cursor;
+    B->meas_blocks = (uint32_t)macc;
     e = upload(B, 0, B->lay.off_T);
     if (e != hipSuccess) return bfail(B, HMC_EHIP, "uploading the batch table", e);
     drop_graphs(B);
@@ -626,14 +638,33 @@ int hmc_batch_observables(hmc_batch* B, hmc_obs* out)
     } catch (...) {
         return bfail(B, HMC_ENOMEM, "host memory for the device states");
     }
-    for (size_t i = 0; i < n; ++i) {
-        int st = hmc::enqueue_observables(B->lat[i], &s[i]);
-        if (st != HMC_OK) {
-            (void)hipStreamSynchronize(B->stream);
-            return bfail(B, st, hmc_last_error(B->lat[i]));
+    bool timed = false;
+    for (const hmc_lattice* L : B->lat) timed = timed || L->timer.on;
+    hipError_t e = hipSuccess;
+    if (timed) {
+        // a lattice counts its launches: one measurement after the other
+        for (size_t i = 0; i < n; ++i) {
+            int st = hmc::enqueue_observables(B->lat[i], &s[i]);
+            if (st != HMC_OK) {
+                (void)hipStreamSynchronize(B->stream);
+                return bfail(B, st, hmc_last_error(B->lat[i]));
+            }
+        }
+        e = hipStreamSynchronize(B->stream);
+    } else {
+        int st = refresh_table(B);
+        if (st != HMC_OK) return st;
+        // the states land in a staging buffer, which the device writes itself
+        e = staging_wait(B);
+        if (e == hipSuccess)
+            e = hmc::launch_measure_batch(B->precision, B->ws + B->lay.off_tab, B->meas_start, (uint32_t)n,
+                                          B->meas_blocks, reinterpret_cast<hmc::DevState*>(B->staging), B->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(B->stream);
+        if (e == hipSuccess) {
+            memcpy(s.data(), B->staging, n * sizeof(hmc::DevState));
+            for (hmc_lattice* L : B->lat) L->m_valid = true;
         }
     }
-    hipError_t e = hipStreamSynchronize(B->stream);
     if (e != hipSuccess) return bfail(B, HMC_EHIP, "reading the device states", e);
     int worst = HMC_OK;
     for (size_t i = 0; i < n; ++i) {

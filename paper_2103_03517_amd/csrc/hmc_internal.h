@@ -112,6 +112,9 @@ hipError_t launch_constrained(const DevLattice& d, int step, const double eC[3],
 // colour, flags fin) together with the colour-0 records of the next sweep.
 hipError_t launch_finalize_nbsum(const DevLattice& d, int64_t rec_blocks, int fin, double T, hipStream_t s);
 hipError_t launch_measure(const DevLattice& d, hipStream_t s, int64_t* blocks);
+// Planes per thread and work-groups of the measurement.
+int measure_planes(const DevLattice& d);
+int64_t measure_blocks(const DevLattice& d);
 // Mean spin of each z plane into out[3*nz] (device memory).
 hipError_t launch_plane_means(const DevLattice& d, double* out, hipStream_t s);
 // Reduces the counts of the colour-0 (red_blocks) and colour-1 (black_blocks)
@@ -160,6 +163,12 @@ hipError_t launch_pass_batch(int precision, const BatchLaunch& b, int colour, bo
 // T[i] is its temperature.
 hipError_t launch_finalize_batch(int precision, const void* tab, uint32_t count, const double* T,
                                  const int32_t* fin, hipStream_t s);
+// The measurement of every lattice of a batch in two launches: lattice i owns
+// the work-groups [start[i], start[i+1]) (device memory) of the first;
+// work-group i of the second folds its records and copies its state to
+// out[i] (memory the device can write).
+hipError_t launch_measure_batch(int precision, const void* tab, const uint32_t* start, uint32_t count, uint32_t nblk,
+                                DevState* out, hipStream_t s);
 // Work-group i clears lattice i's accumulators.
 hipError_t launch_reset_batch(int precision, const void* tab, uint32_t count, hipStream_t s);
 

@@ -125,56 +125,6 @@ __global__ __launch_bounds__(kThreads) void init_kernel(const KArgs<R> a, int mo
 
 
 // ---------------------------------------------------------------------------
-// Neighbour sum of colour index k of colour C (its six neighbours are of the
-// other colour), in the order x-, x+, y-, y+, z-, z+; also the other-colour
-// x-partner with the same index.  Used by the gather kernels.
-// ---------------------------------------------------------------------------
-template <typename R, int C>
-__device__ __forceinline__ void gather_neighbours(const KArgs<R>& a, const Arrays<R>& g, uint32_t k, V3<R>& nb,
-                                                  V3<R>& partner, uint32_t& site)
-{
-    constexpr int O = 1 - C;
-    constexpr uint32_t rs = sizeof(R);
-    const uint32_t hx = a.hx, ny = a.ny, nz = a.nz, P = a.P;
-    const uint32_t kx = k % hx, r = k / hx;
-    const uint32_t y = r % ny, z = r / ny;
-    const uint32_t p = (y + z + (uint32_t)C) & 1u;
-    site = 2u * k + p;
-    const uint32_t row = k - kx;                      // hx*(y + ny*z)
-    const uint32_t d = p ? (kx == hx - 1 ? row : k + 1) : (kx == 0 ? row + hx - 1 : k - 1);
-    const uint32_t fz = P * z;
-    const uint32_t ym = kx + hx * (y == 0 ? ny - 1 : y - 1) + fz;
-    const uint32_t yp = kx + hx * (y == ny - 1 ? 0 : y + 1) + fz;
-    const uint32_t inpl = kx + hx * y;
-    const uint32_t zm = inpl + P * (z == 0 ? nz - 1 : z - 1);
-    const uint32_t zp = inpl + P * (z == nz - 1 ? 0 : z + 1);
-    const V3<R> same = g.get(O, k * rs, 0), xd = g.get(O, d * rs, 0);
-    const V3<R> vym = g.get(O, ym * rs, 0), vyp = g.get(O, yp * rs, 0);
-    V3<R> vzm = g.get(O, zm * rs, 0), vzp = g.get(O, zp * rs, 0);
-    if (a.zbound) {
-        if (z == 0) vzm = across_z(vzm, a.zbound);
-        if (z == nz - 1) vzp = across_z(vzp, a.zbound);
-    }
-    V3<R> xm = p ? same : xd;
-    V3<R> xp = p ? xd : same;
-    V3<R> v2 = vym, v3 = vyp;
-    if (a.mask[C]) {
-        const uint32_t mb = a.mask[C][k];
-        const V3<R> zero{R(0), R(0), R(0)};
-        if (!(mb & 1u)) xm = zero;
-        if (!(mb & 2u)) xp = zero;
-        if (!(mb & 4u)) v2 = zero;
-        if (!(mb & 8u)) v3 = zero;
-        if (!(mb & 16u)) vzm = zero;
-        if (!(mb & 32u)) vzp = zero;
-    }
-    nb = V3<R>{((((xm.x + xp.x) + v2.x) + v3.x) + vzm.x) + vzp.x,
-               ((((xm.y + xp.y) + v2.y) + v3.y) + vzm.y) + vzp.y,
-               ((((xm.z + xp.z) + v2.z) + v3.z) + vzm.z) + vzp.z};
-    partner = same;
-}
-
-// ---------------------------------------------------------------------------
 // Constrained sweep (Table A2).  A constrained call works on an AoS copy of
 // the spins (one 4-vector per site, both colours), made on entry and copied
 // back on exit.  Before each colour's pair pass a stencil kernel writes, for
@@ -524,28 +474,14 @@ __global__ __launch_bounds__(kThreads) void pair_kernel(const KArgs<R> a, Vec4<R
     block_end<R, OBS>(ra, C, blockIdx.x, nacc, acc, scratch);
 }
 
-// ---------------------------------------------------------------------------
-// Measurement of the current spins: one thread per colour index k covers the
-// black site k (with its six red neighbours: every bond once) and the red
-// site k; the last work-group stores M, the energies and the torque.
-// ---------------------------------------------------------------------------
 template <typename R>
-__global__ __launch_bounds__(kThreads) void measure_kernel(const KArgs<R> a)
+__global__ __launch_bounds__(kThreads) void measure_kernel(const KArgs<R> a, const uint32_t zc)
 {
     __shared__ double scratch[8 * kNumPart];
-    const Arrays<R> g(a);
-    const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
+    const uint32_t b = xcd_remap(blockIdx.x, gridDim.x);
     Acc acc;
-    if (k < a.Nc) {
-        V3<R> nb, red;
-        uint32_t site;
-        gather_neighbours<R, 1>(a, g, k, nb, red, site);
-        const V3<R> blk = g.get(1, k * (uint32_t)sizeof(R), 0);
-        acc.ex += (double)(-a.m.J * dot(blk, nb));
-        add_site<R, true>(acc, a.m, blk);
-        add_site<R, true>(acc, a.m, red);
-    }
-    block_end<R, true>(a, 1, blockIdx.x, 0u, acc, scratch);
+    measure_column<R>(a, zc, b * kThreads + threadIdx.x, acc);
+    block_end<R, true>(a, 1, b, 0u, acc, scratch);
 }
 
 // Mean spin of every z plane (both colours), for wall profiles: work-group z
@@ -747,11 +683,31 @@ hipError_t launch_plane_means(const DevLattice& d, double* out, hipStream_t s)
     return hipGetLastError();
 }
 
+// Planes per thread of the measurement: the shortest slabs that give 512
+// work-groups at most, which shares the work-group sums where the chip is not
+// filled anyway; above eight planes the shortest that give 2048 (eight to a
+// compute unit).  The rule depends on the lattice alone: hmc_measure_static and
+// a batch measure with the same grid, so with the same bits.
+int measure_planes(const DevLattice& d)
+{
+    auto planes = [&](uint64_t blocks) {
+        const uint64_t slabs = blocks * kThreads / (uint64_t)d.P;
+        return slabs == 0 ? d.nz : (int)cdiv((uint64_t)d.nz, slabs);
+    };
+    const int few = planes(512), many = planes(2048);
+    return few <= 8 ? few : (many > 8 ? many : 8);
+}
+
+int64_t measure_blocks(const DevLattice& d)
+{
+    return (int64_t)cdiv((uint64_t)d.P * cdiv((uint64_t)d.nz, (uint64_t)measure_planes(d)), kThreads);
+}
+
 hipError_t launch_measure(const DevLattice& d, hipStream_t s, int64_t* blocks)
 {
-    const uint32_t grid = cdiv((uint64_t)d.Nc, kThreads);
-    if (d.precision == 32) measure_kernel<float><<<grid, kThreads, 0, s>>>(make_args<float>(d));
-    else measure_kernel<double><<<grid, kThreads, 0, s>>>(make_args<double>(d));
+    const uint32_t grid = (uint32_t)measure_blocks(d), zc = (uint32_t)measure_planes(d);
+    if (d.precision == 32) measure_kernel<float><<<grid, kThreads, 0, s>>>(make_args<float>(d), zc);
+    else measure_kernel<double><<<grid, kThreads, 0, s>>>(make_args<double>(d), zc);
     *blocks = grid;
     return hipGetLastError();
 }

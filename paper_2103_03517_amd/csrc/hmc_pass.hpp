@@ -82,7 +82,8 @@ static KArgs<R> make_args(const DevLattice& d)
 template <typename R>
 struct BatchEntry {
     KArgs<R> a;
-    uint32_t zc, nqb, nblk, pad;
+    uint32_t zc, nqb, nblk;
+    uint32_t mzc;        // planes per thread of the measurement
     double N;
 };
 
@@ -1072,6 +1073,89 @@ struct PassLaunch {
         return hipGetLastError();
     }
 };
+
+// ---------------------------------------------------------------------------
+// Measurement of the current spins: M, the energies and the torque.  A thread
+// takes one column of a slab of zc planes: for each of its colour indices k
+// the black site k with its six red neighbours (every bond once) and the red
+// site k.  The red planes z-1, z and z+1 of the column rotate through
+// registers; the in-plane neighbours are loaded again, from cache.  Threads
+// number the columns of all slabs through, so thin lattices leave none idle.
+//
+// The bytes ask for one read of the spins; what a one-site-per-thread launch
+// spent its time on is the work-group sum of ten doubles, about as many
+// instructions as the 64 sites of a wave.  A slab shares that sum between its
+// planes (measured on MI355X with its finalize against one site per thread:
+// 256^3 FP32 57 us for 116, 464^3 330 for 686, 256^3 FP64 116 for 144).
+// Every term is formed in the spin precision and added in FP64.
+// ---------------------------------------------------------------------------
+template <typename R>
+__device__ __forceinline__ void measure_column(const KArgs<R>& a, const uint32_t zc, const uint32_t f, Acc& acc)
+{
+    constexpr uint32_t rs = sizeof(R);
+    const uint32_t hx = a.hx, ny = a.ny, nz = a.nz, P = a.P;
+    const uint32_t slab = f / P, q = f - slab * P;
+    const uint32_t z0 = slab * zc;
+    if (z0 >= nz) return;
+    const uint32_t zn = min(zc, nz - z0);
+    const uint32_t y = q / hx, kx = q - y * hx;
+    const Arrays<R> g(a);
+    // distance to the x-neighbour that is not the same-index partner, by the
+    // x parity of the black site, and to the y-neighbours (in sites)
+    const int32_t d0 = kx == 0 ? (int32_t)hx - 1 : -1, d1 = kx == hx - 1 ? 1 - (int32_t)hx : 1;
+    const int32_t dm = y == 0 ? (int32_t)(hx * (ny - 1)) : -(int32_t)hx;
+    const int32_t dp = y == ny - 1 ? -(int32_t)(hx * (ny - 1)) : (int32_t)hx;
+    uint32_t k = q + P * z0;
+    V3<R> om = g.get(0, (z0 == 0 ? q + P * (nz - 1) : k - P) * rs, 0);
+    V3<R> o0 = g.get(0, k * rs, 0);
+    // what a step reads: the red plane above, the black site, the in-plane
+    // neighbours and the mask
+    struct Step {
+        V3<R> op, blk, xd, ym, yp;
+        uint32_t mb;
+    };
+    auto load = [&](uint32_t z, uint32_t i, Step& s) {
+        s.op = g.get(0, (z == nz - 1 ? q : i + P) * rs, 0);
+        s.blk = g.get(1, i * rs, 0);
+        s.xd = g.get(0, (i + (uint32_t)(((y + z + 1u) & 1u) ? d1 : d0)) * rs, 0);
+        s.ym = g.get(0, (i + (uint32_t)dm) * rs, 0);
+        s.yp = g.get(0, (i + (uint32_t)dp) * rs, 0);
+        s.mb = a.mask[1] ? a.mask[1][i] : 0x3Fu;
+    };
+    if (a.zbound && z0 == 0) om = across_z(om, a.zbound);
+    Step cur;
+    load(z0, k, cur);
+    const uint32_t zl = z0 + zn - 1;
+    for (uint32_t z = z0; z <= zl; ++z) {
+        // the next step's loads leave before this step's sums (the last step
+        // loads its own again: behind a branch the waits come early, 464^3
+        // FP32 359 us for 330)
+        Step next;
+        load(min(z + 1u, zl), z < zl ? k + P : k, next);
+        if (a.zbound && z == nz - 1) cur.op = across_z(cur.op, a.zbound);
+        const uint32_t p = (y + z + 1u) & 1u;
+        V3<R> xm = p ? o0 : cur.xd, xp = p ? cur.xd : o0, zm = om, zp = cur.op;
+        if (a.mask[1]) {
+            const V3<R> zero{R(0), R(0), R(0)};
+            if (!(cur.mb & 1u)) xm = zero;
+            if (!(cur.mb & 2u)) xp = zero;
+            if (!(cur.mb & 4u)) cur.ym = zero;
+            if (!(cur.mb & 8u)) cur.yp = zero;
+            if (!(cur.mb & 16u)) zm = zero;
+            if (!(cur.mb & 32u)) zp = zero;
+        }
+        const V3<R> nb{((((xm.x + xp.x) + cur.ym.x) + cur.yp.x) + zm.x) + zp.x,
+                       ((((xm.y + xp.y) + cur.ym.y) + cur.yp.y) + zm.y) + zp.y,
+                       ((((xm.z + xp.z) + cur.ym.z) + cur.yp.z) + zm.z) + zp.z};
+        acc.ex += (double)(-a.m.J * dot(cur.blk, nb));
+        add_site<R, true>(acc, a.m, cur.blk);
+        add_site<R, true>(acc, a.m, o0);
+        om = o0;
+        o0 = cur.op;
+        cur = next;
+        k += P;
+    }
+}
 
 // The colour pass of a lattice with bond masks (hmc_masked_kernels.hip).
 hipError_t launch_pass_masked(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s);

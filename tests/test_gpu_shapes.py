@@ -52,3 +52,40 @@ def test_batch_default_shape(H, shape, precision, default):
         alone.sweep(0.8, n, sample=smp)
     assert alone.get_state() == inb.get_state()
     B.close()
+
+
+# one plane per thread, a ragged last slab, eight planes and more, thin
+# lattices whose slabs share a work-group, one plane, several record groups
+@pytest.mark.parametrize("shape,boundary", [((2, 2, 2), "periodic"), ((6, 4, 38), "antiperiodic"), ((2, 2, 2050), "periodic"),
+                                            ((16, 18, 7), "open"), ((34, 10, 1), "open"), ((130, 128, 70), "antiperiodic"),
+                                            ((256, 254, 190), "periodic")])
+@pytest.mark.parametrize("precision", [32, 64])
+def test_measurement_against_numpy(H, shape, boundary, precision):
+    nx, ny, nz = shape
+    kw = dict(J=1.1, Ku=0.03, eu=(0.2, -0.4, 0.9), Kc=-0.02, h=(0.01, 0.02, -0.015))
+    g = H.Lattice(*shape, precision=precision, boundary_z=boundary, init="random", seed=7, **kw)
+    o = g.observables()
+    S = g.spins().reshape(nz, ny, nx, 3)
+    e = np.asarray(kw["eu"]) / np.linalg.norm(kw["eu"])
+    up = np.roll(S, -1, axis=0)
+    up[-1] *= {"periodic": 1.0, "antiperiodic": -1.0, "open": 0.0}[boundary]
+    ex = -kw["J"] * (S * (np.roll(S, -1, axis=2) + np.roll(S, -1, axis=1) + up)).sum()
+    q = S ** 2
+    un = -kw["Ku"] * ((S @ e) ** 2).sum()
+    cu = kw["Kc"] * (q[..., 0] * q[..., 1] + q[..., 0] * q[..., 2] + q[..., 1] * q[..., 2]).sum()
+    ze = -(S @ np.asarray(kw["h"])).sum()
+    grad = 2 * kw["Ku"] * (S @ e)[..., None] * e - 2 * kw["Kc"] * S * (q.sum(-1, keepdims=True) - q)
+    def total(v):       # pairwise sums: numpy adds a strided axis term after term
+        return np.array([np.ascontiguousarray(v[..., i]).sum() for i in range(3)])
+
+    tq = total(np.cross(S, grad))
+    # each of N terms rounded a few times (unit roundoff u), errors of random sign, the sums in FP64
+    tol = 40 * np.sqrt(g.n) * (2.0 ** -24 if precision == 32 else 2.0 ** -50)
+    assert np.allclose(o["M"], total(S), rtol=0, atol=tol)
+    assert np.allclose([o["E_exch"], o["E_uni"], o["E_cub"], o["E_zee"]], [ex, un, cu, ze], rtol=1e-7 if precision == 32 else 1e-14,
+                       atol=tol)
+    assert np.allclose(o["torque"], tq, rtol=0, atol=tol)
+    B = H.Batch([H.Lattice(4, 4, 4, precision=precision, seed=2), g])
+    b = B.observables()[1]
+    assert all(b[k] == o[k] for k in b)
+    B.close()
