@@ -120,7 +120,8 @@ typedef struct {
 } hmc_obs;
 
 /* Per-kernel timing collected with HIP events on the handle's stream while
- * timing is enabled.  Kinds: 0 = standard colour pass, 1 = constrained pair
+ * timing is enabled.  Kinds: 0 = standard colour pass (on small lattices a
+ * whole sweep), 1 = constrained pair
  * pass, 2 = reductions (the per-sweep finalize: cone angle, counters,
  * accumulators, with the parallel fold of the work-group records that comes
  * before it on large lattices; and the measurement of the current spins),
@@ -237,7 +238,9 @@ int hmc_set_state(hmc_lattice* L, const void* host_buf, size_t bytes);
  * 1 site per thread where that leaves short slabs, else 2; above 256 MiB (the
  * march that loads two planes ahead) 2 sites per thread with z_chunk 8 at
  * FP32 and 32 at FP64 (16 with bond masks).  hmc_get_launch gives the shape
- * hmc_sweep uses.  In a batch, a lattice whose shape was not set takes a
+ * hmc_sweep uses; lattices of up to 600000 spins at FP32 (300000 at FP64) for
+ * which neither a shape nor a look-ahead was set take a whole sweep per
+ * launch instead, with the same spins.  In a batch, a lattice whose shape was not set takes a
  * default of its own: (1, 4), and (2, 8) for FP64 lattices above 64^3 spins.
  * Errors: HMC_EINVAL. */
 int hmc_set_launch(hmc_lattice* L, int32_t sites_per_thread, int32_t z_chunk);

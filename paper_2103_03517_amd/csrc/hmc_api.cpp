@@ -320,6 +320,7 @@ int hmc_init_lattice(const hmc_params* p, void* dev_ws, size_t ws_bytes, void* h
     }
     hmc::default_shape(d, &L->spt, &L->zc);
     hmc::default_batch_shape(d, &L->batch_spt, &L->batch_zc);
+    L->whole = hmc::sweep_plan(d, &L->plan);
     memset(&L->init_state, 0, sizeof(L->init_state));
     L->init_state.theta = p->theta0_deg;
 
@@ -342,6 +343,24 @@ int hmc_sweep(hmc_lattice* L, double T, int32_t n_sweeps, int32_t sample)
     if (!(T > 0.0) || !isfinite(T)) return fail(L, HMC_EINVAL, "temperature must be positive and finite");
     if (n_sweeps < 0) return fail(L, HMC_EINVAL, "n_sweeps must be >= 0");
     const bool obs = sample != 0;
+    // small lattices: a launch per sweep, unless a launch shape or a look-ahead
+    // of the passes was set
+    if (L->whole && !L->shape_set && L->d.prefetch == 0) {
+        if (n_sweeps == 0) return HMC_OK;
+        int st = HMC_OK;
+        const int32_t odd = n_sweeps & 1;
+        if (odd) st = launch(L, 3, "copy of the spins", [&] { return hmc::launch_sweep_copy(L->d, L->stream); });
+        for (int32_t it = 0; it < n_sweeps && st == HMC_OK; ++it)
+            st = launch(L, 0, "sweep kernel", [&] {
+                return hmc::launch_sweep(L->d, L->plan, it, ((it ^ odd) & 1) == 0, obs, T, L->stream);
+            });
+        if (st == HMC_OK)
+            st = launch(L, 2, "finalize kernel", [&] {
+                return hmc::launch_sweep_finalize(L->d, L->plan, n_sweeps - 1, obs, T, L->stream);
+            });
+        if (st == HMC_OK) L->m_valid = obs;
+        return st;
+    }
     for (int32_t it = 0; it < n_sweeps; ++it) {
         int64_t nr = 0, nb = 0;
         int st = launch(L, 0, "red pass", [&] {
@@ -725,6 +744,7 @@ int hmc_set_launch(hmc_lattice* L, int32_t sites_per_thread, int32_t z_chunk)
         return fail(L, HMC_EINVAL, "launch shape needs more than 64 KiB of LDS");
     L->spt = L->batch_spt = sites_per_thread;
     L->zc = L->batch_zc = z_chunk;
+    L->shape_set = true;
     return HMC_OK;
 }
 

@@ -121,6 +121,20 @@ hipError_t launch_plane_means(const DevLattice& d, double* out, hipStream_t s);
 // launches and the partials of part_blocks work-groups into the state.
 hipError_t launch_finalize(const DevLattice& d, int64_t red_blocks, int64_t black_blocks, int64_t part_blocks,
                            int fin, double T, hipStream_t s);
+// Whole sweeps in one launch (hmc_sweep_kernels.hip): launch 0, 1, ... of a call
+// reads the spins and writes their copy in the constrained scratch (to_copy),
+// or the other way; launch_sweep_finalize closes the call's last one.
+// launch_sweep_copy makes the copy for a call that begins from it.
+// sweep_plan: false where the lattice has no such plan.
+struct SweepPlan {
+    int32_t ry = 0, zc = 0;      // rows and planes of a tile
+    int32_t ntile = 0;
+};
+bool sweep_plan(const DevLattice& d, SweepPlan* plan);
+hipError_t launch_sweep_copy(const DevLattice& d, hipStream_t s);
+hipError_t launch_sweep(const DevLattice& d, const SweepPlan& p, int launch, bool to_copy, bool obs, double T,
+                        hipStream_t s);
+hipError_t launch_sweep_finalize(const DevLattice& d, const SweepPlan& p, int launch, bool obs, double T, hipStream_t s);
 // Number of work-groups of the standard pass for a launch shape.
 int64_t pass_blocks(const DevLattice& d, int spt, int zc);
 // Dynamic LDS bytes of the standard pass for a launch shape.
