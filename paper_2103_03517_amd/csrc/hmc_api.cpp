@@ -605,56 +605,21 @@ int hmc_copy_spins(hmc_lattice* L, double* host_xyz, int32_t to_host)
 {
     if (!L || !host_xyz) return HMC_EINVAL;
     const DevLattice& d = L->d;
-    const size_t rs = d.precision / 8;
-    const size_t bytes = (size_t)d.Nc * rs;
-    std::vector<char> buf;
-    try {
-        buf.resize(6 * bytes);
-    } catch (...) {
-        return fail(L, HMC_ENOMEM, "host staging buffer");
-    }
-    char* base = static_cast<char*>(d.spins);
-    auto get = [&](int c, int a, int64_t k) -> double {
-        const char* p = buf.data() + (size_t)(3 * c + a) * bytes;
-        return d.precision == 64 ? reinterpret_cast<const double*>(p)[k] : (double)reinterpret_cast<const float*>(p)[k];
-    };
-    auto put = [&](int c, int a, int64_t k, double v) {
-        char* p = buf.data() + (size_t)(3 * c + a) * bytes;
-        if (d.precision == 64) reinterpret_cast<double*>(p)[k] = v;
-        else reinterpret_cast<float*>(p)[k] = (float)v;
-    };
+    // by way of the constrained working area (free between calls; 32 bytes per
+    // spin at least, of which the doubles in site order take 24)
+    double* xyz = static_cast<double*>(d.aos);
+    const size_t bytes = 3 * sizeof(double) * (size_t)d.N;
     hipError_t e = hipSuccess;
     if (to_host) {
-        for (int i = 0; i < 6 && e == hipSuccess; ++i)
-            e = hipMemcpyAsync(buf.data() + i * bytes, base + i * d.pitch, bytes, hipMemcpyDeviceToHost, L->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-        if (e != hipSuccess) return fail(L, HMC_EHIP, "copying spins to the host", e);
-    }
-    // site id i = 2k + p, colour c = (x + y + z) & 1
-    for (int64_t k = 0; k < d.Nc; ++k) {
-        const int64_t r = k / d.hx;
-        const int64_t y = r % d.ny, z = r / d.ny;
-        for (int c = 0; c < 2; ++c) {
-            const int64_t i = 2 * k + ((y + z + c) & 1);
-            if (to_host) {
-                for (int a = 0; a < 3; ++a) host_xyz[3 * i + a] = get(c, a, k);
-            } else {
-                // directions are normalised on the way in; zero or non-finite
-                // vectors are stored as given
-                const double* v = host_xyz + 3 * i;
-                const double n2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
-                const double inv = (n2 > 0.0 && isfinite(n2)) ? 1.0 / sqrt(n2) : 1.0;
-                for (int a = 0; a < 3; ++a) put(c, a, k, v[a] * inv);
-            }
-        }
-    }
-    if (!to_host) {
-        for (int i = 0; i < 6 && e == hipSuccess; ++i)
-            e = hipMemcpyAsync(base + i * d.pitch, buf.data() + i * bytes, bytes, hipMemcpyHostToDevice, L->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
-        if (e != hipSuccess) return fail(L, HMC_EHIP, "copying spins to the device", e);
+        e = hmc::launch_site_order(d, xyz, false, L->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(host_xyz, xyz, bytes, hipMemcpyDeviceToHost, L->stream);
+    } else {
+        e = hipMemcpyAsync(xyz, host_xyz, bytes, hipMemcpyHostToDevice, L->stream);
+        if (e == hipSuccess) e = hmc::launch_site_order(d, xyz, true, L->stream);
         L->m_valid = false;
     }
+    if (e == hipSuccess) e = hipStreamSynchronize(L->stream);
+    if (e != hipSuccess) return fail(L, HMC_EHIP, to_host ? "copying spins to the host" : "copying spins to the device", e);
     return HMC_OK;
 }
 

@@ -98,6 +98,8 @@ hipError_t launch_init(const DevLattice& d, hipStream_t s);
 // Zeroes the chain state (cone angle theta0) and writes the cone table, 181
 // doubles at c1_dev followed by the same 181 values as floats.
 hipError_t launch_setup(const DevLattice& d, const double* c1d_host, int theta0, void* c1_dev, hipStream_t s);
+// The spins from (in) or to 3 N doubles in site order at xyz (device memory).
+hipError_t launch_site_order(const DevLattice& d, double* xyz, bool in, hipStream_t s);
 // Splits N bytes of bond masks in site order at src (device) into the
 // colour-split mask array of the lattice.
 hipError_t launch_split_masks(const DevLattice& d, const uint8_t* src, hipStream_t s);

@@ -89,3 +89,30 @@ def test_measurement_against_numpy(H, shape, boundary, precision):
     b = B.observables()[1]
     assert all(b[k] == o[k] for k in b)
     B.close()
+
+
+@pytest.mark.parametrize("shape", [(2, 2, 2), (6, 10, 4), (258, 2, 6), (64, 36, 30)])
+@pytest.mark.parametrize("precision", [32, 64])
+def test_spins_in_site_order(H, shape, precision):
+    """Spins read back are the ones given, divided by their length as numpy
+    does it in double precision and rounded to the lattice's; zero and
+    non-finite vectors are kept."""
+    n = shape[0] * shape[1] * shape[2]
+    v = np.random.default_rng(n).normal(size=(n, 3)) * 3.0
+    v[1], v[2], v[3, 1] = 0.0, (np.inf, 1.0, -2.0), np.nan
+    n2 = (v[:, 0] * v[:, 0] + v[:, 1] * v[:, 1]) + v[:, 2] * v[:, 2]
+    with np.errstate(divide="ignore", invalid="ignore"):
+        inv = np.where((n2 > 0) & np.isfinite(n2), 1.0 / np.sqrt(n2), 1.0)
+    g = H.Lattice(*shape, precision=precision)
+    g.set_spins(v)
+    want = v * inv[:, None]
+    if precision == 32:
+        want = want.astype(np.float32).astype(np.float64)
+    assert np.array_equal(g.spins(), want, equal_nan=True)
+    # the component arrays at the head of the workspace: site 2k + p, colour (x + y + z) & 1
+    rs, half = precision // 8, n // 2
+    pitch = (half * rs + 255) // 256 * 256
+    raw = g.workspace[:6 * pitch].cpu().numpy().view(np.float32 if rs == 4 else np.float64).reshape(6, -1)[:, :half]
+    x, y, z = (i.T.reshape(-1) for i in np.indices(shape))
+    for c in (0, 1):
+        assert np.array_equal(raw[3 * c:3 * c + 3].T, want[(x + y + z) % 2 == c], equal_nan=True)
