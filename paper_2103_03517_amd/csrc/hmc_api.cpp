@@ -400,9 +400,20 @@ int hmc_constrained_sweep(hmc_lattice* L, double T, const double eC[3], int32_t 
         return launch(L, kind, what, [&] { return launch_constrained(L->d, which, e, T, L->stream, &nb); });
     };
     int st = step(3, hmc::kAosIn, "copy to the AoS working copy");
-    if (st == HMC_OK) st = step(3, hmc::kNbRed, "red neighbour sums");
     const int fin = hmc::kFinCounts | hmc::kFinObs | hmc::kFinTorque | (sample ? hmc::kFinSample : 0);
-    for (int32_t it = 0; it < n_sweeps && st == HMC_OK; ++it) {
+    const bool direct = hmc::pair_direct(L->d);
+    auto pairs = [&](int kind, int colour, int32_t it, const char* what) {
+        return launch(L, kind, what, [&] { return hmc::launch_pair_direct(L->d, colour, it, e, T, fin, L->stream); });
+    };
+    if (direct) {
+        for (int32_t it = 0; it < n_sweeps && st == HMC_OK; ++it) {
+            st = pairs(1, 0, it, "red pair pass");
+            if (st == HMC_OK) st = pairs(1, 1, it, "black pair pass");
+        }
+        if (st == HMC_OK) st = pairs(2, 2, n_sweeps - 1, "finalize kernel");
+    }
+    if (!direct && st == HMC_OK) st = step(3, hmc::kNbRed, "red neighbour sums");
+    for (int32_t it = 0; !direct && it < n_sweeps && st == HMC_OK; ++it) {
         st = step(1, hmc::kPairRed, "red pair pass");
         if (st == HMC_OK) st = step(3, hmc::kNbBlack, "black neighbour sums");
         if (st == HMC_OK) st = step(1, hmc::kPairBlack, "black pair pass");

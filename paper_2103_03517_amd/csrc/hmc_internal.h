@@ -110,6 +110,12 @@ hipError_t launch_pass(const DevLattice& d, int colour, bool obs, int spt, int z
 enum ConstrainedStep { kAosIn = 0, kNbRed, kPairRed, kNbBlack, kPairBlack, kAosOut };
 hipError_t launch_constrained(const DevLattice& d, int step, const double eC[3], double T, hipStream_t s,
                               int64_t* blocks);
+// Constrained sweeps without records, for small lattices: the pair pass of
+// colour 0 or 1 of sweep `sweep` of a call, which also finalizes the sweep
+// before; colour 2: the finalize of that sweep, the call's last.
+bool pair_direct(const DevLattice& d);
+hipError_t launch_pair_direct(const DevLattice& d, int colour, int sweep, const double eC[3], double T, int fin,
+                              hipStream_t s);
 // The finalize of a constrained sweep (pair records of rec_blocks rows per
 // colour, flags fin) together with the colour-0 records of the next sweep.
 hipError_t launch_finalize_nbsum(const DevLattice& d, int64_t rec_blocks, int fin, double T, hipStream_t s);

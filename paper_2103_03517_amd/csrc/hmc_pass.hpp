@@ -552,6 +552,157 @@ __device__ __forceinline__ void finalize_body(DevState* st, const double* part, 
 }
 
 // ---------------------------------------------------------------------------
+// The finalize where a launch folds the records of the sweep before beside its
+// own work (hmc_sweep_kernels.hip, pair_direct_kernel).
+// ---------------------------------------------------------------------------
+// Row `row` of n records, by one wave: lane l adds records l, l + 64, ..., then
+// the lanes are summed.
+__device__ __forceinline__ double fold_row(const double* part, uint32_t row, uint32_t n)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const double* p = part + (size_t)row * n;
+    double x = 0.0;
+    for (uint32_t i0 = 0; i0 < n; i0 += 512u) {
+        double q[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) q[u] = p[min(i0 + u * 64u + lane, n - 1u)];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) x += i0 + u * 64u + lane < n ? q[u] : 0.0;
+    }
+    return wave_sum(x);
+}
+
+// The counts of n records, by one wave.
+__device__ __forceinline__ unsigned long long fold_counts(const uint32_t* cnt, uint32_t n)
+{
+    unsigned long long c = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += 512u) {
+        uint32_t q[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) q[u] = cnt[min(i0 + u * 64u + (threadIdx.x & 63u), n - 1u)];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) c += i0 + u * 64u + (threadIdx.x & 63u) < n ? q[u] : 0u;
+    }
+    return wave_sum(c);
+}
+
+// The record of a work-group of NT threads: its NV sums, row e at
+// row0[e * stride], and its count.  The values change places in LDS (buf: NV * NT
+// doubles, free on entry), a wave then sums a row: where a launch is one
+// update deep, a tree for every row in every wave (block_sum) was a tenth of it
+// (2400 of 23000 cycles of a pair pass at 32^3, MI355X).
+template <int NT, int NV>
+__device__ __forceinline__ void write_record(const double (&v)[NV], uint32_t nacc, double* row0, size_t stride,
+                                             uint32_t* cnt, double* buf, uint32_t* wtot)
+{
+    constexpr uint32_t NW = NT / 64;
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+#pragma unroll
+    for (int e = 0; e < NV; ++e) buf[e * NT + t] = v[e];
+    const uint32_t c = wave_sum(nacc);
+    if (lane == 0) wtot[wave] = c;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t e0 = 0; e0 < (uint32_t)NV; e0 += NW) {
+        const uint32_t e = e0 + wave;
+        if (e < (uint32_t)NV) {
+            double x = 0.0;
+#pragma unroll
+            for (uint32_t u = 0; u < NW; ++u) x += buf[e * NT + u * 64u + lane];
+            x = wave_sum(x);
+            if (lane == 0) row0[e * stride] = x;
+        }
+    }
+    if (t == (uint32_t)NT - 1) {
+        uint32_t tot = 0;
+        for (uint32_t w = 0; w < NW; ++w) tot += wtot[w];
+        *cnt = tot;
+    }
+}
+
+// The finalize of a sweep from n records (rows of n partials and a row of
+// counts), by a work-group of NT threads: theta rule, sweep counter, and by the
+// flags the observables, the torque and the accumulators, as finalize_body.  A
+// wave folds a row; the state update runs across lanes, and its old values are
+// fetched with the records: in finalize_body's form, one thread's chain of
+// divisions and stores, this work-group took 13000 cycles where the tiles of
+// a 16^3 sweep took 9000 (MI355X).  tot: NR doubles and totc in shared memory.
+template <int NT, int NR>
+__device__ __forceinline__ void fold_sweep(DevState* st, const double* part, const uint32_t* cnt, uint32_t n, int fin,
+                                           double T, double N, double* tot, unsigned long long* totc)
+{
+    constexpr uint32_t NW = NT / 64;
+    static_assert(NR == kObsRows || NR == kTorqueRows, "rows of a record");
+    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
+    // the old state, one value per lane of wave 0: accumulator i of lanes 0..4,
+    // that of the anisotropy energy in lane 5, of the torque in lanes 7..9
+    double shift = 0.0, sum = 0.0, sum2 = 0.0;
+    int32_t theta = 0;
+    int64_t samples = 0, torque_samples = 0, sweep = 0;
+    if (wave == 0) {
+        const uint32_t i = min(lane, 4u);
+        shift = st->shift[i];
+        sum = lane == 5 ? st->sum_eanis : (lane >= 7 ? st->sum_torque[min(lane - 7u, 2u)] : st->sum[i]);
+        sum2 = st->sum2[i];
+        samples = st->samples;
+        torque_samples = st->torque_samples;
+        theta = st->theta;
+        sweep = st->sweep;
+    }
+    for (uint32_t row = wave; row <= (uint32_t)NR; row += NW) {
+        if (row == (uint32_t)NR) {
+            const unsigned long long c = fold_counts(cnt, n);
+            if (lane == 0) *totc = c;
+        } else if (fin & kFinObs) {
+            const double x = fold_row(part, row, n);
+            if (lane == 0) tot[row] = x;
+        }
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    const long long accepted = (long long)*totc;
+    if (lane == 0) {
+        st->accepted_last = accepted;
+        if (2.0 * (double)accepted > N) theta = theta < 180 ? theta + 1 : theta;
+        else theta = theta > 1 ? theta - 1 : theta;
+        st->theta = theta;
+        st->sweep = sweep + 1;
+    }
+    if (!(fin & kFinObs)) return;
+    const double row = tot[min(lane, (uint32_t)NR - 1u)];
+    if (__ballot(!isfinite(row)) && lane == 0) st->nonfinite = 1;
+    double* inst = st->M;                        // M[3], the four energies, the torque[3]
+    if (lane < (uint32_t)NR) inst[lane] = row;
+    if (!(fin & kFinSample)) return;
+    // lane 1, 2, 3: m_x, m_y, m_z; lane 4: E/N; lane 5: (E_uni + E_cub)/N; lanes
+    // 7..9: the torque; lane 0: |m|
+    double num = lane < 4 ? tot[lane == 0 ? 0u : lane - 1u] : row;
+    if (lane == 4) num = tot[kEexch] + tot[kEuni] + tot[kEcub] + tot[kEzee];
+    if (lane == 5) num = tot[kEuni] + tot[kEcub];
+    double x = num / N;
+    const double mx = read_lane(x, 1), my = read_lane(x, 2), mz = read_lane(x, 3);
+    const double ml = sqrt(mx * mx + my * my + mz * mz);
+    if (lane == 0) x = ml;
+    if (lane < 5) {
+        const double sh = samples == 0 ? x : shift, d = x - sh;
+        if (samples == 0) st->shift[lane] = x;
+        st->sum[lane] = sum + d;
+        st->sum2[lane] = sum2 + d * d;
+    } else if (lane == 5) {
+        st->sum_eanis = sum + x;
+    } else if (lane == 6) {
+        st->samples = samples + 1;
+        st->T_sample = T;
+        if (NR == kTorqueRows) st->torque_samples = torque_samples + 1;
+    } else if (NR == kTorqueRows && lane < 10) {
+        st->sum_torque[lane - 7u] = sum + x;
+    }
+}
+static_assert(offsetof(DevState, E_exch) == offsetof(DevState, M) + 24 && offsetof(DevState, E_zee) == offsetof(DevState, M) + 48 &&
+                  offsetof(DevState, torque) == offsetof(DevState, M) + 56,
+              "M, the energies and the torque lie in the order of the rows");
+
+// ---------------------------------------------------------------------------
 // The Metropolis update of one site (Table A1, Eq. 1, Eq. 2): cone proposal,
 // energy change in the local field, acceptance P < exp(-dE/T).  Returns the
 // final spin; OBS adds the site and its red x-partner to the observables.

@@ -128,94 +128,6 @@ __device__ __forceinline__ V3<R> tile_neighbours(const Lds<R, S>& o, uint32_t e,
                  ((((o0.z + xd.z) + ym.z) + yp.z) + zm.z) + zp.z};
 }
 
-// The finalize of a sweep from the records of its n tiles, by a work-group of
-// NT threads: theta rule, sweep counter and (kFinObs) the observables and
-// accumulators, as finalize_body.  A wave folds a row: lane l adds records l,
-// l + 64, ..., then the lanes are summed.  The state update runs across lanes,
-// and its old values are fetched with the records: in finalize_body's form,
-// one thread's chain of divisions and stores, this work-group took 13000
-// cycles where the tiles took 9000 (16^3 FP32).
-template <int NT>
-__device__ __forceinline__ void fold_sweep(DevState* st, const double* part, const uint32_t* cnt, uint32_t n, int fin,
-                                           double T, double N, double* tot, unsigned long long* totc)
-{
-    constexpr uint32_t NW = NT / 64;
-    constexpr uint32_t kRow = 7;                 // the row index of the counts
-    static_assert(kObsRows == 7, "rows of a record");
-    const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    // the old state, one value per lane of wave 0: accumulator i of lanes 0..4,
-    // that of the anisotropy energy in lane 5
-    double shift = 0.0, sum = 0.0, sum2 = 0.0;
-    int32_t theta = 0;
-    int64_t samples = 0, sweep = 0;
-    if (wave == 0) {
-        const uint32_t i = min(lane, 4u);
-        shift = st->shift[i];
-        sum = lane == 5 ? st->sum_eanis : st->sum[i];
-        sum2 = st->sum2[i];
-        samples = st->samples;
-        theta = st->theta;
-        sweep = st->sweep;
-    }
-    for (uint32_t row = wave; row <= kRow; row += NW) {
-        if (row == kRow) {
-            unsigned long long c = 0;
-            for (uint32_t i = lane; i < n; i += 64u) c += cnt[i];
-            c = wave_sum(c);
-            if (lane == 0) *totc = c;
-        } else if (fin & kFinObs) {
-            const double* p = part + (size_t)row * n;
-            double x = 0.0;
-            for (uint32_t i0 = 0; i0 < n; i0 += 512u) {
-                double q[8];
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) {
-                    const uint32_t i = i0 + u * 64u + lane;
-                    q[u] = p[min(i, n - 1u)];
-                }
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) x += i0 + u * 64u + lane < n ? q[u] : 0.0;
-            }
-            x = wave_sum(x);
-            if (lane == 0) tot[row] = x;
-        }
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    const long long accepted = (long long)*totc;
-    if (lane == 0) {
-        st->accepted_last = accepted;
-        if (2.0 * (double)accepted > N) theta = theta < 180 ? theta + 1 : theta;
-        else theta = theta > 1 ? theta - 1 : theta;
-        st->theta = theta;
-        st->sweep = sweep + 1;
-    }
-    if (!(fin & kFinObs)) return;
-    const double row = tot[min(lane, 6u)];
-    if (__ballot(!isfinite(row)) && lane == 0) st->nonfinite = 1;
-    double* inst = st->M;                        // M[3], then the four energies
-    if (lane < (uint32_t)kObsRows) inst[lane] = row;
-    // lane 1, 2, 3: m_x, m_y, m_z; lane 4: E/N; lane 5: (E_uni + E_cub)/N; lane 0: |m|
-    const double e = lane == 4 ? tot[kEexch] + tot[kEuni] + tot[kEcub] + tot[kEzee] : tot[kEuni] + tot[kEcub];
-    double x = (lane < 4 ? tot[lane == 0 ? 0u : lane - 1u] : e) / N;
-    const double mx = read_lane(x, 1), my = read_lane(x, 2), mz = read_lane(x, 3);
-    const double ml = sqrt(mx * mx + my * my + mz * mz);
-    if (lane == 0) x = ml;
-    if (lane < 5) {
-        const double sh = samples == 0 ? x : shift, d = x - sh;
-        if (samples == 0) st->shift[lane] = x;
-        st->sum[lane] = sum + d;
-        st->sum2[lane] = sum2 + d * d;
-    } else if (lane == 5) {
-        st->sum_eanis = sum + x;
-    } else if (lane == 6) {
-        st->samples = samples + 1;
-        st->T_sample = T;
-    }
-}
-static_assert(offsetof(DevState, E_exch) == offsetof(DevState, M) + 24 && offsetof(DevState, E_zee) == offsetof(DevState, M) + 48,
-              "M and the energies lie in the order of the rows");
-
 // The finalize of the last sweep of a call, by the work-group size that does the others.
 template <typename R>
 __global__ __launch_bounds__(TileCap<R>::threads) void sweep_finalize_kernel(DevState* st, const double* part,
@@ -224,7 +136,7 @@ __global__ __launch_bounds__(TileCap<R>::threads) void sweep_finalize_kernel(Dev
 {
     __shared__ double tot[kObsRows];
     __shared__ unsigned long long totc;
-    fold_sweep<TileCap<R>::threads>(st, part, cnt, n, fin, T, N, tot, &totc);
+    fold_sweep<TileCap<R>::threads, kObsRows>(st, part, cnt, n, fin, T, N, tot, &totc);
 }
 
 // The six component arrays, from one copy to the other.
@@ -241,14 +153,14 @@ __global__ __launch_bounds__(TileCap<R>::threads) void sweep_kernel(const KArgs<
     constexpr int NB = SB / NT, NR = (SR + NT - 1) / NT;      // black loads and red sites per thread
     static_assert(SB % NT == 0, "black sites per thread");
     __shared__ __align__(16) R smem[3 * (SB + SR)];
-    __shared__ double scratch[kObsRows * (NW + 1)];
+    __shared__ double tot[kObsRows];
     __shared__ unsigned long long totc;
     __shared__ uint32_t wacc[NW], wtot[NW];
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
     const uint32_t prev = f.parity ^ 1u;
     if (blockIdx.x == f.ntile) {
-        fold_sweep<NT>(a.st, f.part + (size_t)prev * kObsRows * f.ntile, f.cnt + (size_t)prev * f.ntile, f.ntile, f.fin,
-                       f.T, f.N, scratch, &totc);
+        fold_sweep<NT, kObsRows>(a.st, f.part + (size_t)prev * kObsRows * f.ntile, f.cnt + (size_t)prev * f.ntile, f.ntile, f.fin,
+                       f.T, f.N, tot, &totc);
         return;
     }
     const uint32_t tile = xcd_remap(blockIdx.x, f.ntile);
@@ -403,27 +315,23 @@ __global__ __launch_bounds__(TileCap<R>::threads) void sweep_kernel(const KArgs<
         d[2 * pitch] = n.z;
     }
     if constexpr (OBS) flush_part(acc, pa);
-    // the tile's record: counts as integers, sums over the waves in order
-    const uint32_t na = wave_sum(nacc);
-    if (lane == 0) wtot[wave] = na;
-    if (OBS) {
-        double v[kObsRows] = {acc.M[0], acc.M[1], acc.M[2], acc.ex, acc.eu, acc.ec, acc.ez};
-#pragma unroll
-        for (int e = 0; e < kObsRows; ++e) v[e] = wave_sum(v[e]);
-        if (lane == 0)
-#pragma unroll
-            for (int e = 0; e < kObsRows; ++e) scratch[wave * kObsRows + e] = v[e];
-    }
-    __syncthreads();
-    if (OBS && t < (uint32_t)kObsRows) {
-        double s = 0.0;
-        for (int w = 0; w < NW; ++w) s += scratch[w * kObsRows + t];
-        f.part[((size_t)f.parity * kObsRows + t) * f.ntile + tile] = s;
-    }
-    if (t == 64) {
-        uint32_t tot = 0;
-        for (int w = 0; w < NW; ++w) tot += wtot[w];
-        f.cnt[(size_t)f.parity * f.ntile + tile] = tot;
+    // the tile's record
+    uint32_t* cnt = f.cnt + (size_t)f.parity * f.ntile + tile;
+    if constexpr (OBS) {
+        static_assert(kObsRows * NT * sizeof(double) <= sizeof(smem), "the record's sums change places in the tile");
+        const double v[kObsRows] = {acc.M[0], acc.M[1], acc.M[2], acc.ex, acc.eu, acc.ec, acc.ez};
+        __syncthreads();                      // the tile's spins have been read
+        write_record<NT, kObsRows>(v, nacc, f.part + (size_t)f.parity * kObsRows * f.ntile + tile, f.ntile, cnt,
+                                   reinterpret_cast<double*>(smem), wtot);
+    } else {
+        const uint32_t na = wave_sum(nacc);
+        if (lane == 0) wtot[wave] = na;
+        __syncthreads();
+        if (t == 0) {
+            uint32_t tot = 0;
+            for (int w = 0; w < NW; ++w) tot += wtot[w];
+            *cnt = tot;
+        }
     }
 }
 
