@@ -318,6 +318,7 @@ int hmc_init_lattice(const hmc_params* p, void* dev_ws, size_t ws_bytes, void* h
         L->c1d[th] = 2.0 * s * s;
         L->c1f[th] = (float)L->c1d[th];
     }
+    for (int i = 0; i < 3; ++i) d.geom[i] = hmc::pass_geometry(d.hx, d.ny, 1 << i);
     hmc::default_shape(d, &L->spt, &L->zc);
     hmc::default_batch_shape(d, &L->batch_spt, &L->batch_zc);
     L->whole = hmc::sweep_plan(d, &L->plan);
@@ -716,7 +717,7 @@ int hmc_set_launch(hmc_lattice* L, int32_t sites_per_thread, int32_t z_chunk)
     if (sites_per_thread != 1 && sites_per_thread != 2 && sites_per_thread != 4)
         return fail(L, HMC_EINVAL, "sites_per_thread must be 1, 2 or 4");
     if (z_chunk < 1 || z_chunk > 1024) return fail(L, HMC_EINVAL, "z_chunk must be in [1, 1024]");
-    if (hmc::pass_lds_bytes(L->d.precision, L->d.hx, sites_per_thread) > hmc::kMaxLds)
+    if (!hmc::pass_shape_ok(L->d.precision, L->d.hx, sites_per_thread))
         return fail(L, HMC_EINVAL, "launch shape needs more than 64 KiB of LDS");
     L->spt = L->batch_spt = sites_per_thread;
     L->zc = L->batch_zc = z_chunk;

@@ -221,8 +221,10 @@ int refresh_table(hmc_batch* B)
                 const hmc_lattice* L = B->lat[m[j]];
                 start[j] = (uint32_t)acc;
                 ent[j] = m[j];
-                acc += (uint64_t)hmc::pass_blocks(L->d, L->batch_spt, L->batch_zc);
-                lds = std::max(lds, hmc::pass_lds_bytes(B->precision, L->d.hx, L->batch_spt));
+                const int64_t blocks = hmc::pass_blocks(L->d, L->batch_spt, L->batch_zc);
+                if (blocks > L->d.max_blocks) return bfail(B, HMC_EINVAL, "launch shape leaves more records than a workspace holds");
+                acc += (uint64_t)blocks;
+                lds = std::max(lds, hmc::pass_lds_bytes(L->d, L->batch_spt));
             }
             if (acc > 0x7FFFFFFFull)
                 return bfail(B, HMC_EINVAL, "batch needs more than 2^31 work-groups per launch");
@@ -568,7 +570,7 @@ int hmc_batch_tune(hmc_batch* B, const double* T, int32_t trial_sweeps)
         float best_ms = 0.f;
         st = time_chunked(&best_ms);
         for (int spt : {1, 2, 4}) {
-            if (hmc::pass_lds_bytes(B->precision, L0->d.hx, spt) > hmc::kMaxLds) continue;
+            if (!hmc::pass_shape_ok(B->precision, L0->d.hx, spt)) continue;
             for (int zc = 2; zc <= 64 && zc <= L0->d.nz && st == HMC_OK; zc *= 2) {
                 if (std::make_pair(spt, zc) == best) continue;
                 for (size_t i : members) {

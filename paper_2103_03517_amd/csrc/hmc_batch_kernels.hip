@@ -91,18 +91,17 @@ __global__ __launch_bounds__(kThreads) void finalize_measure_batch_kernel(const 
 // its entry in the batch table and scale[ent[i]] its -1/T.  Each tile runs
 // exactly as in the single-lattice launch, so every lattice evolves bit for
 // bit as it would alone.
-template <typename R, int C, bool OBS, int SPT, int HALO>
-__global__ __launch_bounds__(kThreads) void pass_batch_kernel(const BatchEntry<R>* __restrict__ tab,
-                                                              const uint32_t* __restrict__ start,
-                                                              const uint32_t* __restrict__ ent, const uint32_t n,
-                                                              const uint32_t nblk, const R* __restrict__ scale)
+template <typename R, int C, bool OBS, int SPT, int GEO>
+__global__ __launch_bounds__(kThreads) void pass_batch_kernel(const BatchEntry<R>* __restrict__ tab, const uint32_t* __restrict__ start,
+                       const uint32_t* __restrict__ ent, const uint32_t n, const uint32_t nblk,
+                       const R* __restrict__ scale)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t gb = xcd_remap(blockIdx.x, nblk);
     const uint32_t lo = owner_of(start, n, gb);
     const uint32_t e = ent[lo];
     const BatchEntry<R>& E = tab[e];
-    pass_tile<R, C, OBS, SPT, HALO, false, false>(E.a, E.zc, E.nqb, gb - start[lo], scale[e], smem);
+    pass_tile<R, C, OBS, SPT, GEO, false, false>(E.a, E.geom, E.zc, gb - start[lo], scale[e], smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -112,9 +111,6 @@ size_t batch_entry_bytes(int precision)
 {
     return precision == 32 ? sizeof(BatchEntry<float>) : sizeof(BatchEntry<double>);
 }
-
-int batch_group(const DevLattice& d, int spt) { return (spt == 1 ? 0 : spt == 2 ? 1 : 2) * 3 +
-                                                      (halo_slots(d.hx) == 1 ? 0 : halo_slots(d.hx) == 2 ? 1 : 2); }
 
 void batch_store_scale(int precision, double T, void* dst, size_t i)
 {
@@ -129,7 +125,7 @@ static void fill_entry(void* dst, const DevLattice& d, int spt, int zc)
     memset(&E, 0, sizeof(E));
     E.a = make_args<R>(d);
     E.zc = (uint32_t)zc;
-    E.nqb = cdiv((uint64_t)d.P, (uint64_t)kThreads * spt);
+    E.geom = pass_geom(d, spt);
     E.nblk = (uint32_t)pass_blocks(d, spt, zc);
     E.mzc = (uint32_t)measure_planes(d);
     E.N = (double)d.N;
@@ -142,32 +138,32 @@ void batch_fill_entry(void* dst, const DevLattice& d, int spt, int zc)
     else fill_entry<double>(dst, d, spt, zc);
 }
 
-template <typename R, int SPT, int HALO>
+template <typename R, int SPT, int GEO>
 static void pass_batch_go(const BatchLaunch& b, int colour, bool obs, hipStream_t s)
 {
     const auto* tab = static_cast<const BatchEntry<R>*>(b.tab);
     const auto* sc = static_cast<const R*>(b.scale);
     if (colour == 0)
-        pass_batch_kernel<R, 0, false, SPT, HALO><<<b.nblk, kThreads, b.lds, s>>>(tab, b.start, b.ent, b.n, b.nblk, sc);
+        pass_batch_kernel<R, 0, false, SPT, GEO><<<b.nblk, kThreads, b.lds, s>>>(tab, b.start, b.ent, b.n, b.nblk, sc);
     else if (obs)
-        pass_batch_kernel<R, 1, true, SPT, HALO><<<b.nblk, kThreads, b.lds, s>>>(tab, b.start, b.ent, b.n, b.nblk, sc);
+        pass_batch_kernel<R, 1, true, SPT, GEO><<<b.nblk, kThreads, b.lds, s>>>(tab, b.start, b.ent, b.n, b.nblk, sc);
     else
-        pass_batch_kernel<R, 1, false, SPT, HALO><<<b.nblk, kThreads, b.lds, s>>>(tab, b.start, b.ent, b.n, b.nblk, sc);
+        pass_batch_kernel<R, 1, false, SPT, GEO><<<b.nblk, kThreads, b.lds, s>>>(tab, b.start, b.ent, b.n, b.nblk, sc);
 }
 
 template <typename R>
 static void pass_batch_dispatch(const BatchLaunch& b, int colour, bool obs, hipStream_t s)
 {
     switch (b.group) {
-    case 0: pass_batch_go<R, 1, 1>(b, colour, obs, s); break;
-    case 1: pass_batch_go<R, 1, 2>(b, colour, obs, s); break;
-    case 2: pass_batch_go<R, 1, 4>(b, colour, obs, s); break;
-    case 3: pass_batch_go<R, 2, 1>(b, colour, obs, s); break;
-    case 4: pass_batch_go<R, 2, 2>(b, colour, obs, s); break;
-    case 5: pass_batch_go<R, 2, 4>(b, colour, obs, s); break;
-    case 6: pass_batch_go<R, 4, 1>(b, colour, obs, s); break;
-    case 7: pass_batch_go<R, 4, 2>(b, colour, obs, s); break;
-    default: pass_batch_go<R, 4, 4>(b, colour, obs, s); break;
+    case 0: pass_batch_go<R, 1, 0>(b, colour, obs, s); break;
+    case 1: pass_batch_go<R, 1, 1>(b, colour, obs, s); break;
+    case 2: pass_batch_go<R, 1, 2>(b, colour, obs, s); break;
+    case 3: pass_batch_go<R, 2, 0>(b, colour, obs, s); break;
+    case 4: pass_batch_go<R, 2, 1>(b, colour, obs, s); break;
+    case 5: pass_batch_go<R, 2, 2>(b, colour, obs, s); break;
+    case 6: pass_batch_go<R, 4, 0>(b, colour, obs, s); break;
+    case 7: pass_batch_go<R, 4, 1>(b, colour, obs, s); break;
+    default: pass_batch_go<R, 4, 2>(b, colour, obs, s); break;
     }
 }
 

@@ -10,7 +10,6 @@
 namespace hmc {
 
 constexpr int kThreads = 256;        // work-group size of every kernel
-constexpr int kMaxHalo = 4;          // halo slots per thread: nx <= 1024
 constexpr int kNumPart = 12;         // doubles per work-group partial
 constexpr size_t kAlign = 256;
 constexpr size_t kMaxLds = 64 * 1024;  // dynamic LDS budget of one work-group
@@ -57,6 +56,17 @@ struct DevState {
     double T_sample;
 };
 
+// In-plane windows or tiles of the colour pass for a number of sites per thread.
+struct PassGeom {
+    uint32_t tx, ty;      // columns and rows of a tile (tx * ty <= 256 * sites per thread); 0: windows
+    uint32_t ntx, n;      // tiles across a row; windows or tiles of a plane
+    uint32_t entries;     // LDS entries of a plane: window or tile, with its halo
+};
+
+// The geometry of rows of hx colour sites: windows with one or two halo sites
+// per thread, or tiles (0).
+inline int geometry_of(int hx) { return 2 * hx <= kThreads ? 1 : (hx <= kThreads ? 2 : 0); }
+
 // Everything a kernel launcher needs about one lattice.
 struct DevLattice {
     int32_t precision;        // 32 or 64
@@ -82,7 +92,11 @@ struct DevLattice {
     int32_t zbound;           // z boundary: 0 periodic, 1 anti-periodic, 2 open
     uint8_t* mask;            // [colour][Nc] active-bond bits, or null (every bond)
     int32_t prefetch;         // look-ahead of the standard pass: 0 automatic, 1 or 2 planes
+    PassGeom geom[3];         // for 1, 2 and 4 sites per thread
 };
+
+PassGeom pass_geometry(int hx, int ny, int spt);
+inline const PassGeom& pass_geom(const DevLattice& d, int spt) { return d.geom[spt == 4 ? 2 : spt - 1]; }
 
 // The march depth of a lattice: as set, or automatically two for spins
 // larger than the last-level cache; always one with bond masks.
@@ -145,8 +159,10 @@ hipError_t launch_sweep(const DevLattice& d, const SweepPlan& p, int launch, boo
 hipError_t launch_sweep_finalize(const DevLattice& d, const SweepPlan& p, int launch, bool obs, double T, hipStream_t s);
 // Number of work-groups of the standard pass for a launch shape.
 int64_t pass_blocks(const DevLattice& d, int spt, int zc);
-// Dynamic LDS bytes of the standard pass for a launch shape.
-size_t pass_lds_bytes(int precision, int hx, int spt);
+// Dynamic LDS bytes of the standard pass for a launch shape, and whether the
+// interface accepts the shape.
+size_t pass_lds_bytes(const DevLattice& d, int spt);
+bool pass_shape_ok(int precision, int hx, int spt);
 // Launch shape (sites per thread, z chunk) of the standard pass where none was
 // set: of a lattice swept alone, and of one swept in a batch.
 void default_shape(const DevLattice& d, int* spt, int* zc);
@@ -160,10 +176,10 @@ inline int64_t fold_groups_for(int64_t n) { return (n + 1023) / 1024; }
 // Batches.  The table of a batch holds one entry per lattice (kernel
 // arguments and launch shape), built on the host by batch_fill_entry.  The
 // lattices of one colour-pass launch share a kernel variant: batch_group
-// names it (sites per thread and halo slots, 9 classes).
+// names it (sites per thread and geometry, 9 classes).
 size_t batch_entry_bytes(int precision);
 void batch_fill_entry(void* dst, const DevLattice& d, int spt, int zc);
-int batch_group(const DevLattice& d, int spt);
+inline int batch_group(const DevLattice& d, int spt) { return 3 * (spt == 4 ? 2 : spt - 1) + geometry_of(d.hx); }
 // Stores the Boltzmann scale the kernels use for temperature T (float or
 // double by precision) at element i of dst (host memory).
 void batch_store_scale(int precision, double T, void* dst, size_t i);

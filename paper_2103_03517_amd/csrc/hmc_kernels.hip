@@ -16,12 +16,58 @@
 
 namespace hmc {
 
-size_t pass_lds_bytes(int precision, int hx, int spt)
+// In-plane windows or tiles of the colour pass.  Tiles: the width (a row cut
+// into equal parts) and height that cost least, where a site costs its own
+// accesses and its tile's share of the halo (a third: the caches hold most of
+// it), and threads without a site cost as much as others.  Parts are 48 to 127
+// sites: wide enough for runs of lines, and with one halo site per thread.  Two
+// thirds of the threads of a one-site shape have a site at least, so a pass
+// has no more work-groups than a workspace holds records for (max_blocks_for:
+// twice as many as full ones; launch_pass checks it).
+PassGeom pass_geometry(int hx, int ny, int spt)
 {
-    const size_t W = (size_t)kThreads * spt + 2 * (size_t)hx;
-    const size_t e = precision == 32 ? LdsPlane<float>::bytes_per_entry : LdsPlane<double>::bytes_per_entry;
-    const size_t b = 2 * W * e;
+    const uint32_t most = (uint32_t)kThreads * (uint32_t)spt;
+    PassGeom best{};
+    if (geometry_of(hx) != 0) {
+        best.n = cdiv((uint64_t)hx * ny, most);
+        best.entries = most + 2u * (uint32_t)hx;
+        return best;
+    }
+    double cost = 0.0;
+    for (uint32_t parts = cdiv((uint64_t)hx, 127); parts <= (uint32_t)hx / 48u; ++parts) {
+        const uint32_t tx = cdiv((uint64_t)hx, parts);
+        uint32_t ty = most / tx;
+        if (ty > (uint32_t)kThreads - 2u * tx) ty = (uint32_t)kThreads - 2u * tx;
+        if (ty > (uint32_t)ny) ty = (uint32_t)ny;
+        ty = cdiv((uint64_t)ny, cdiv((uint64_t)ny, ty));                 // equal rows
+        const uint32_t ntx = cdiv((uint64_t)hx, tx), nty = cdiv((uint64_t)ny, ty);
+        const double used = (double)hx * ny / ((double)ntx * nty * most);
+        const double halo = (2.0 * tx + ty) / ((double)tx * ty);
+        const double c = (1.0 + halo / 3.0) / used;
+        if (best.tx == 0 || c < cost) {
+            cost = c;
+            best.tx = tx;
+            best.ty = ty;
+            best.ntx = ntx;
+            best.n = ntx * nty;
+            best.entries = (ty + 2u) * tx + ty + 1u;                     // and one spare
+        }
+    }
+    return best;
+}
+
+size_t pass_lds_bytes(const DevLattice& d, int spt)
+{
+    const size_t e = d.precision == 32 ? LdsPlane<float>::bytes_per_entry : LdsPlane<double>::bytes_per_entry;
+    const size_t b = 2 * (size_t)pass_geom(d, spt).entries * e;
     return b < 1024 ? 1024 : b;
+}
+
+// (the line is that of a window of whole rows, which the pass once kept)
+bool pass_shape_ok(int precision, int hx, int spt)
+{
+    const size_t e = precision == 32 ? LdsPlane<float>::bytes_per_entry : LdsPlane<double>::bytes_per_entry;
+    return 2 * ((size_t)kThreads * spt + 2 * (size_t)hx) * e <= kMaxLds;
 }
 
 // The per-sweep finalize, one work-group of 1024 threads: all of them sum
@@ -744,7 +790,7 @@ int64_t max_blocks_for(int32_t nx, int32_t ny, int32_t nz)
 
 int64_t pass_blocks(const DevLattice& d, int spt, int zc)
 {
-    return (int64_t)cdiv((uint64_t)d.P, (uint64_t)kThreads * spt) * (int64_t)cdiv((uint64_t)d.nz, (uint64_t)zc);
+    return (int64_t)pass_geom(d, spt).n * (int64_t)cdiv((uint64_t)d.nz, (uint64_t)zc);
 }
 
 // The launch shape where none was set.  A step of the march is bound by the
@@ -752,7 +798,9 @@ int64_t pass_blocks(const DevLattice& d, int spt, int zc)
 // cache holds takes the shortest slabs whose work-groups still run in one
 // round: kRoundBlocks of them (four of 256 threads to a compute unit at FP32,
 // two at FP64, whose march holds twice the registers).  One site per thread
-// while that leaves short slabs, else two, which share a slab's fixed cost.
+// while that leaves short slabs, else two, which share a slab's fixed cost
+// (rows above 256 sites, whose tiles are narrow: always one, 1024 x 1024 x 5 with
+// masks (1, 5) 51.7 us, (2, 5) 55; 1024 x 512 x 15 (1, 15) 67, (2, 8) 74).
 // Measured on MI355X, sampled sweeps, against (2, 16): 32^3 FP32 (1, 1) 13.3
 // us for 47.8, 128^3 (1, 4) 27.8 for 51.3, 192^3 (2, 8) 60.7 for 72.6, 256^3
 // (2, 16) 110.6 and every other shape above 116; FP64 32^3 (1, 1) 15.3 for
@@ -762,7 +810,7 @@ int64_t pass_blocks(const DevLattice& d, int spt, int zc)
 // re-read fewer slab ends (256^3 FP64 63.9 G updates/s for 62.8 with 16).
 void default_shape(const DevLattice& d, int* spt, int* zc)
 {
-    const bool wide = pass_lds_bytes(d.precision, d.hx, 2) > kMaxLds;   // no room for two sites per thread
+    const bool wide = !pass_shape_ok(d.precision, d.hx, 2);
     if (pass_deep(d) || (uint64_t)d.N * 3ull * (uint64_t)(d.precision / 8) > kDeepMarchBytes) {
         *spt = wide ? 1 : 2;
         *zc = d.mask ? 16 : (d.precision == 32 ? 8 : 32);
@@ -771,12 +819,12 @@ void default_shape(const DevLattice& d, int* spt, int* zc)
     constexpr int kRoundBlocks[2] = {1024, 512}, kShortSlab[2] = {4, 8};   // FP32, FP64
     const int p = d.precision == 32 ? 0 : 1;
     for (int s = 1; s <= 2; ++s) {
-        const int nqb = (int)cdiv((uint64_t)d.P, (uint64_t)kThreads * s);
+        const int nqb = (int)pass_geom(d, s).n;
         const int slabs = kRoundBlocks[p] / nqb;                         // as many as one round holds
         const int planes = slabs > 0 ? (int)cdiv((uint64_t)d.nz, (uint64_t)slabs) : d.nz;
         *spt = s;
         *zc = planes < 16 ? planes : 16;
-        if (*zc <= kShortSlab[p] || (s == 1 && wide)) return;
+        if (*zc <= kShortSlab[p] || (s == 1 && (wide || geometry_of(d.hx) == 0))) return;
     }
 }
 
@@ -792,7 +840,7 @@ void default_batch_shape(const DevLattice& d, int* spt, int* zc)
         default_shape(d, spt, zc);
         return;
     }
-    const bool two = d.precision == 64 && d.N > (int64_t)64 * 64 * 64 && pass_lds_bytes(64, d.hx, 2) <= kMaxLds;
+    const bool two = d.precision == 64 && d.N > (int64_t)64 * 64 * 64 && pass_shape_ok(64, d.hx, 2);
     *spt = two ? 2 : 1;
     *zc = two ? 8 : 4;
 }
@@ -836,6 +884,7 @@ hipError_t launch_pass(const DevLattice& d, int colour, bool obs, int spt, int z
                        int64_t* blocks)
 {
     *blocks = pass_blocks(d, spt, zc);
+    if (*blocks > d.max_blocks) return hipErrorInvalidValue;
     if (d.mask) return launch_pass_masked(d, colour, obs, spt, zc, T, s);
     if (pass_deep(d)) return launch_pass_deep(d, colour, obs, spt, zc, T, s);
     return PassLaunch<false, false>::run(d, colour, obs, spt, zc, T, s);

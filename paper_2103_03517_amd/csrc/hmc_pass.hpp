@@ -82,7 +82,8 @@ static KArgs<R> make_args(const DevLattice& d)
 template <typename R>
 struct BatchEntry {
     KArgs<R> a;
-    uint32_t zc, nqb, nblk;
+    PassGeom geom;       // in-plane tiles of the colour pass
+    uint32_t zc, nblk;
     uint32_t mzc;        // planes per thread of the measurement
     double N;
 };
@@ -191,13 +192,6 @@ template <> struct LdsPlane<double> {
 };
 
 static inline uint32_t cdiv(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
-
-// Halo slots per thread of the standard pass (a template argument).
-static inline int halo_slots(int hx)
-{
-    const int halo = (2 * hx + kThreads - 1) / kThreads;
-    return halo <= 1 ? 1 : (halo == 2 ? 2 : 4);
-}
 
 // Work-groups are dispatched round-robin over the 8 XCDs (each with its own
 // L2).  Renumber them so that XCD x receives one contiguous range of logical
@@ -739,12 +733,24 @@ __device__ __forceinline__ V3<R> update_site(const Model<R>& m, const V3<R>& s, 
 // ---------------------------------------------------------------------------
 // Standard colour pass (Table A1, MonteCarlo_Red(Black)ParallelPass).
 //
-// A work-group owns Q = 256*SPT consecutive in-plane colour indices and
-// marches over z_chunk planes.  The other colour's plane z sits in LDS as a
-// window [base - hx, base + Q + hx) (the x and y neighbours), so each plane
-// of each colour is fetched once per pass (plus a halo of 2*hx entries per
-// plane).  Two marches share this layout and differ in how far ahead the
-// loads run:
+// A work-group owns up to 256*SPT in-plane sites of one colour and marches over
+// z_chunk planes.  The other colour's plane z sits in LDS with the x and y
+// neighbours of the owned sites, so each plane of each colour is fetched once
+// per pass, plus a halo.  Two geometries (GEO):
+//
+// * a window of consecutive colour indices, [base - hx, base + Q + hx) with the
+//   halo (GEO 1 or 2: halo sites per thread): every access is one run of lines;
+// * where rows are longer than 256 sites of a colour (GEO 0), a tile of tx
+//   columns of ty rows, with a row more above and below and for each row the
+//   one site beyond its edge that an x neighbour can be (left or right, by the
+//   row's parity in that plane).  A window of one row of 512 fetched two rows
+//   beside it.
+//
+// Short rows keep the window: its halo comes from the caches, and the tiles'
+// broken lines cost more (measured on MI355X, us per sampled sweep: tiles
+// against windows in each one's best shape, masked 1024 x 1024 x 5 52 for 64, 1024
+// x 512 x 15 67 for 86; 464^3 FP32 937 for 757, 256^3 FP64 284 for 262).
+// Two marches share this layout and differ in how far ahead the loads run:
 //
 // * depth one (march1): step z issues the other colour's plane z+2 and the
 //   own colour's plane z+1; the other colour's z-1, z, z+1 and z+2 values at
@@ -764,31 +770,60 @@ __device__ __forceinline__ V3<R> update_site(const Model<R>& m, const V3<R>& s, 
 // its z chunk (z_chunk x SPT sites) and converts the sums to FP64 once;
 // everything above the thread is FP64.
 // ---------------------------------------------------------------------------
-template <typename R, int SPT, int HALO>
+template <int GEO> constexpr int kHaloSlots = GEO == 2 ? 2 : 1;
+
+template <typename R, int SPT, int GEO>
 struct PassCtx {
-    uint32_t hx, P, nz, W, z0, zn;
+    static constexpr int NH = kHaloSlots<GEO>;
+    uint32_t tx, P, nz, W, z0, zn;   // tx: LDS entries from row to row
     uint32_t voff[SPT];          // byte offset of each owned column in a plane
     uint32_t w[SPT];             // its LDS entry
     uint32_t wd[2][SPT];         // LDS entry of its second x-neighbour, by z parity
     uint32_t par[SPT];           // x parity of the column at z = z0
     bool act[SPT];
-    uint32_t hvoff[HALO], hw[HALO];
-    bool hact[HALO];
+    uint32_t hvoff[NH], hw[NH];  // the halo sites this thread fetches and their LDS entries
+    uint32_t hodd;               // GEO 0: the halo site of planes z0 + 1, z0 + 3, ... (hvoff: z0, z0 + 2, ...)
+    bool hact[NH];
+    // the halo site of slot i in planes of parity b
+    __device__ __forceinline__ uint32_t halo(int i, uint32_t b) const { return GEO == 0 && b ? hodd : hvoff[i]; }
     unsigned char* lds[2];
     R c1, scale;
     uint32_t sweep;
     uint32_t zbound;
 };
 
+// The neighbour sum of a site, in the order x-, x+, y-, y+, z-, z+ (o0, the
+// same-index partner, and xd are the x neighbours, p the site's x parity); with
+// MASK, bonds cut by the site's mask (intergrain bonds) weigh zero.
+template <typename R, bool MASK>
+__device__ __forceinline__ V3<R> neighbour_sum(const V3<R>& o0, const V3<R>& xd, uint32_t p, const V3<R>& ym,
+                                               const V3<R>& yp, const V3<R>& zm, const V3<R>& zp, uint32_t mb)
+{
+    if constexpr (MASK) {
+        const V3<R> xm = p ? o0 : xd, xp = p ? xd : o0;
+        const R w0 = (mb & 1u) ? R(1) : R(0), w1 = (mb & 2u) ? R(1) : R(0);
+        const R w2 = (mb & 4u) ? R(1) : R(0), w3 = (mb & 8u) ? R(1) : R(0);
+        const R w4 = (mb & 16u) ? R(1) : R(0), w5 = (mb & 32u) ? R(1) : R(0);
+        return V3<R>{((((w0 * xm.x + w1 * xp.x) + w2 * ym.x) + w3 * yp.x) + w4 * zm.x) + w5 * zp.x,
+                     ((((w0 * xm.y + w1 * xp.y) + w2 * ym.y) + w3 * yp.y) + w4 * zm.y) + w5 * zp.y,
+                     ((((w0 * xm.z + w1 * xp.z) + w2 * ym.z) + w3 * yp.z) + w4 * zm.z) + w5 * zp.z};
+    } else {
+        // x- + x+ is the same sum in either order
+        return V3<R>{((((o0.x + xd.x) + ym.x) + yp.x) + zm.x) + zp.x,
+                     ((((o0.y + xd.y) + ym.y) + yp.y) + zm.y) + zp.y,
+                     ((((o0.z + xd.z) + ym.z) + yp.z) + zm.z) + zp.z};
+    }
+}
+
 // Depth-one march: one step, plane z = z0 + zi; the register planes om, o0,
 // op, opp hold the other colour's z-1, z, z+1 and z+2 (in flight), sc and
-// sn the own colour's z and z+1 (in flight), hp and hpp the halo's z+1 and
-// z+2 (in flight).
-template <typename R, int C, bool OBS, int SPT, int HALO, int K, bool MASK, typename A>
-__device__ __forceinline__ void step1(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, HALO>& x,
-                                          uint32_t zi, V3<R> (&om)[SPT], V3<R> (&o0)[SPT], V3<R> (&op)[SPT],
-                                          V3<R> (&opp)[SPT], V3<R> (&sc)[SPT], V3<R> (&sn)[SPT],
-                                          V3<R> (&hp)[HALO], V3<R> (&hpp)[HALO], uint32_t& nacc, A& acc)
+// sn the own colour's z and z+1 (in flight), mc and mn their masks, hp and hpp
+// the halo's z+1 and z+2 (in flight).
+template <typename R, int C, bool OBS, int SPT, int GEO, int K, bool MASK, typename A>
+__device__ __forceinline__ void step1(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, GEO>& x, uint32_t zi,
+                                      V3<R> (&om)[SPT], V3<R> (&o0)[SPT], V3<R> (&op)[SPT], V3<R> (&opp)[SPT],
+                                      V3<R> (&sc)[SPT], V3<R> (&sn)[SPT], uint32_t (&mc)[SPT], uint32_t (&mn)[SPT],
+                                      V3<R> (&hp)[kHaloSlots<GEO>], V3<R> (&hpp)[kHaloSlots<GEO>], uint32_t& nacc, A& acc)
 {
     constexpr int O = 1 - C;
     constexpr int B = K & 1;
@@ -808,10 +843,11 @@ __device__ __forceinline__ void step1(const KArgs<R>& a, const Arrays<R>& g, con
         for (int j = 0; j < SPT; ++j) {
             opp[j] = g.get(O, x.voff[j], fpp);
             sn[j] = g.get(C, x.voff[j], fn);
+            if (MASK) mn[j] = a.mask[C][x.voff[j] / (uint32_t)sizeof(R) + x.P * (z + 1)];
         }
 #pragma unroll
-        for (int i = 0; i < HALO; ++i)
-            if (x.hact[i]) hpp[i] = g.get(O, x.hvoff[i], fpp);
+        for (int i = 0; i < x.NH; ++i)
+            if (x.hact[i]) hpp[i] = g.get(O, x.halo(i, B), fpp);
         __builtin_amdgcn_s_setprio(0);
         // anti-periodic or open z: plane z + 2 = nz is plane 0 seen across
         // the boundary; it serves only as the z+1 neighbour of plane nz - 1.
@@ -822,6 +858,11 @@ __device__ __forceinline__ void step1(const KArgs<R>& a, const Arrays<R>& g, con
             for (int j = 0; j < SPT; ++j) opp[j] = across_z(opp[j], x.zbound);
         }
     }
+    // the sites' indices are formed here: carried from step to step they cost 4 to 6
+    // registers, and with them a wave per SIMD (a batch of 24 lattices of 48^3 to
+    // 128^3 FP32 in (1, 4): 173 us a sweep for 162 on MI355X)
+    uint32_t pz = x.P * z;
+    asm("" : "+s"(pz));
     const unsigned char* L = x.lds[B];
     const uint32_t fz = plane_off(z);
 #pragma unroll
@@ -829,26 +870,10 @@ __device__ __forceinline__ void step1(const KArgs<R>& a, const Arrays<R>& g, con
         if (!x.act[j]) continue;
         const uint32_t p = x.par[j] ^ (uint32_t)B;
         const V3<R> xd = LdsPlane<R>::get(L, x.W, x.wd[B][j]);
-        const V3<R> ym = LdsPlane<R>::get(L, x.W, x.w[j] - x.hx);
-        const V3<R> yp = LdsPlane<R>::get(L, x.W, x.w[j] + x.hx);
-        const V3<R> xm = p ? o0[j] : xd;
-        const V3<R> xp = p ? xd : o0[j];
-        const uint32_t k = x.voff[j] / (uint32_t)sizeof(R) + x.P * (z >= x.nz ? z - x.nz : z);
-        V3<R> nb;
-        if (MASK) {
-            // bonds cut by the site's mask (intergrain bonds) weigh zero
-            const uint32_t mb = a.mask[C][k];
-            const R w0 = (mb & 1u) ? R(1) : R(0), w1 = (mb & 2u) ? R(1) : R(0);
-            const R w2 = (mb & 4u) ? R(1) : R(0), w3 = (mb & 8u) ? R(1) : R(0);
-            const R w4 = (mb & 16u) ? R(1) : R(0), w5 = (mb & 32u) ? R(1) : R(0);
-            nb = V3<R>{((((w0 * xm.x + w1 * xp.x) + w2 * ym.x) + w3 * yp.x) + w4 * om[j].x) + w5 * op[j].x,
-                       ((((w0 * xm.y + w1 * xp.y) + w2 * ym.y) + w3 * yp.y) + w4 * om[j].y) + w5 * op[j].y,
-                       ((((w0 * xm.z + w1 * xp.z) + w2 * ym.z) + w3 * yp.z) + w4 * om[j].z) + w5 * op[j].z};
-        } else {
-            nb = V3<R>{((((xm.x + xp.x) + ym.x) + yp.x) + om[j].x) + op[j].x,
-                       ((((xm.y + xp.y) + ym.y) + yp.y) + om[j].y) + op[j].y,
-                       ((((xm.z + xp.z) + ym.z) + yp.z) + om[j].z) + op[j].z};
-        }
+        const V3<R> ym = LdsPlane<R>::get(L, x.W, x.w[j] - x.tx);
+        const V3<R> yp = LdsPlane<R>::get(L, x.W, x.w[j] + x.tx);
+        const uint32_t k = x.voff[j] / (uint32_t)sizeof(R) + pz;
+        const V3<R> nb = neighbour_sum<R, MASK>(o0[j], xd, p, ym, yp, om[j], op[j], MASK ? mc[j] : 0u);
         const Rand4 rn = philox(x.sweep, 2u * k + p, (uint32_t)C, a.inst, a.key0, a.key1);
         const V3<R> f = update_site<R, OBS>(a.m, sc[j], nb, o0[j], rn, x.c1, x.scale, nacc, acc);
         g.put(C, x.voff[j], fz, f);
@@ -858,18 +883,19 @@ __device__ __forceinline__ void step1(const KArgs<R>& a, const Arrays<R>& g, con
 #pragma unroll
         for (int j = 0; j < SPT; ++j) LdsPlane<R>::put(Ln, x.W, x.w[j], op[j]);
 #pragma unroll
-        for (int i = 0; i < HALO; ++i)
+        for (int i = 0; i < x.NH; ++i)
             if (x.hact[i]) LdsPlane<R>::put(Ln, x.W, x.hw[i], hp[i]);
     }
     __syncthreads();
 }
 
-template <typename R, int C, bool OBS, int SPT, int HALO, bool MASK>
-__device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, HALO>& x,
-                                       uint32_t& nacc, Acc& acc)
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK>
+__device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, GEO>& x, uint32_t& nacc,
+                                       Acc& acc)
 {
     constexpr int O = 1 - C;
-    V3<R> rA[SPT], rB[SPT], rC[SPT], rD[SPT], s0[SPT], s1[SPT], h0[HALO], h1[HALO];
+    V3<R> rA[SPT], rB[SPT], rC[SPT], rD[SPT], s0[SPT], s1[SPT], h0[kHaloSlots<GEO>], h1[kHaloSlots<GEO>];
+    uint32_t m0[SPT], m1[SPT];
     {
         auto plane_off = [&](int zz) -> uint32_t {
             const int w = zz < 0 ? zz + (int)a.nz : (zz >= (int)a.nz ? zz - (int)a.nz : zz);
@@ -882,12 +908,13 @@ __device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, co
             rB[j] = g.get(O, x.voff[j], f0);
             rC[j] = g.get(O, x.voff[j], fp);
             s0[j] = g.get(C, x.voff[j], f0);
+            if (MASK) m0[j] = a.mask[C][x.voff[j] / (uint32_t)sizeof(R) + a.P * x.z0];
         }
 #pragma unroll
-        for (int i = 0; i < HALO; ++i)
+        for (int i = 0; i < x.NH; ++i)
             if (x.hact[i]) {
-                LdsPlane<R>::put(x.lds[0], x.W, x.hw[i], g.get(O, x.hvoff[i], f0));
-                h0[i] = g.get(O, x.hvoff[i], fp);
+                LdsPlane<R>::put(x.lds[0], x.W, x.hw[i], g.get(O, x.halo(i, 0), f0));
+                h0[i] = g.get(O, x.halo(i, 1), fp);
             }
 #pragma unroll
         for (int j = 0; j < SPT; ++j) LdsPlane<R>::put(x.lds[0], x.W, x.w[j], rB[j]);
@@ -909,16 +936,17 @@ __device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, co
     auto& pa = site_acc<R>(acc, part);
     uint32_t zi = 0;
     for (; zi + 4 <= x.zn; zi += 4) {
-        step1<R, C, OBS, SPT, HALO, 0, MASK>(a, g, x, zi + 0, rA, rB, rC, rD, s0, s1, h0, h1, nacc, pa);
-        step1<R, C, OBS, SPT, HALO, 1, MASK>(a, g, x, zi + 1, rB, rC, rD, rA, s1, s0, h1, h0, nacc, pa);
-        step1<R, C, OBS, SPT, HALO, 2, MASK>(a, g, x, zi + 2, rC, rD, rA, rB, s0, s1, h0, h1, nacc, pa);
-        step1<R, C, OBS, SPT, HALO, 3, MASK>(a, g, x, zi + 3, rD, rA, rB, rC, s1, s0, h1, h0, nacc, pa);
+        step1<R, C, OBS, SPT, GEO, 0, MASK>(a, g, x, zi + 0, rA, rB, rC, rD, s0, s1, m0, m1, h0, h1, nacc, pa);
+        step1<R, C, OBS, SPT, GEO, 1, MASK>(a, g, x, zi + 1, rB, rC, rD, rA, s1, s0, m1, m0, h1, h0, nacc, pa);
+        step1<R, C, OBS, SPT, GEO, 2, MASK>(a, g, x, zi + 2, rC, rD, rA, rB, s0, s1, m0, m1, h0, h1, nacc, pa);
+        step1<R, C, OBS, SPT, GEO, 3, MASK>(a, g, x, zi + 3, rD, rA, rB, rC, s1, s0, m1, m0, h1, h0, nacc, pa);
     }
-    if (zi < x.zn) step1<R, C, OBS, SPT, HALO, 0, MASK>(a, g, x, zi + 0, rA, rB, rC, rD, s0, s1, h0, h1, nacc, pa);
-    if (zi + 1 < x.zn) step1<R, C, OBS, SPT, HALO, 1, MASK>(a, g, x, zi + 1, rB, rC, rD, rA, s1, s0, h1, h0, nacc, pa);
-    if (zi + 2 < x.zn) step1<R, C, OBS, SPT, HALO, 2, MASK>(a, g, x, zi + 2, rC, rD, rA, rB, s0, s1, h0, h1, nacc, pa);
+    if (zi < x.zn) step1<R, C, OBS, SPT, GEO, 0, MASK>(a, g, x, zi + 0, rA, rB, rC, rD, s0, s1, m0, m1, h0, h1, nacc, pa);
+    if (zi + 1 < x.zn)
+        step1<R, C, OBS, SPT, GEO, 1, MASK>(a, g, x, zi + 1, rB, rC, rD, rA, s1, s0, m1, m0, h1, h0, nacc, pa);
+    if (zi + 2 < x.zn)
+        step1<R, C, OBS, SPT, GEO, 2, MASK>(a, g, x, zi + 2, rC, rD, rA, rB, s0, s1, m0, m1, h0, h1, nacc, pa);
     if constexpr (OBS) flush_part(acc, pa);
-
 }
 
 // Depth-two march: one step, plane z = z0 + zi.  op: the other colour's plane
@@ -932,12 +960,12 @@ __device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, co
 // (the compiler's wait counts are then those of the steady state); the
 // planes are clamped to the last one the tile needs, so the loads of the
 // last steps re-read planes just fetched.
-template <typename R, int C, bool OBS, int SPT, int HALO, bool MASK, typename A>
-__device__ __forceinline__ void step2(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, HALO>& x,
-                                          uint32_t zi, V3<R> (&om)[SPT], V3<R> (&op)[SPT], V3<R> (&on)[SPT],
-                                          V3<R> (&sc)[SPT], V3<R> (&sn)[SPT], V3<R> (&hp)[HALO],
-                                          V3<R> (&hn)[HALO], uint32_t (&mc)[SPT], uint32_t (&mn)[SPT],
-                                          uint32_t& nacc, A& acc)
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, typename A>
+__device__ __forceinline__ void step2(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, GEO>& x, uint32_t zi,
+                                      V3<R> (&om)[SPT], V3<R> (&op)[SPT], V3<R> (&on)[SPT], V3<R> (&sc)[SPT],
+                                      V3<R> (&sn)[SPT], V3<R> (&hp)[kHaloSlots<GEO>], V3<R> (&hn)[kHaloSlots<GEO>],
+                                      uint32_t (&mc)[SPT],
+                                      uint32_t (&mn)[SPT], uint32_t& nacc, A& acc)
 {
     constexpr int O = 1 - C;
     const uint32_t z = x.z0 + zi;
@@ -959,7 +987,7 @@ __device__ __forceinline__ void step2(const KArgs<R>& a, const Arrays<R>& g, con
         if (MASK) mn[j] = a.mask[C][x.voff[j] / (uint32_t)sizeof(R) + x.P * z2];
     }
 #pragma unroll
-    for (int i = 0; i < HALO; ++i) hn[i] = g.get(O, x.hvoff[i], f3);
+    for (int i = 0; i < x.NH; ++i) hn[i] = g.get(O, x.halo(i, B ^ 1u), f3);
     // anti-periodic or open z: plane nz is plane 0 seen across the boundary
     // (only ever the z+1 neighbour of plane nz - 1); a uniform branch taken
     // in the top tile only
@@ -975,7 +1003,7 @@ __device__ __forceinline__ void step2(const KArgs<R>& a, const Arrays<R>& g, con
 #pragma unroll
         for (int j = 0; j < SPT; ++j) LdsPlane<R>::put(Ln, x.W, x.w[j], op[j]);
 #pragma unroll
-        for (int i = 0; i < HALO; ++i)
+        for (int i = 0; i < x.NH; ++i)
             if (x.hact[i]) LdsPlane<R>::put(Ln, x.W, x.hw[i], hp[i]);
     }
     const unsigned char* L = B ? x.lds[1] : x.lds[0];
@@ -985,27 +1013,11 @@ __device__ __forceinline__ void step2(const KArgs<R>& a, const Arrays<R>& g, con
         if (!x.act[j]) continue;
         const uint32_t p = x.par[j] ^ B;
         const V3<R> xd = LdsPlane<R>::get(L, x.W, B ? x.wd[1][j] : x.wd[0][j]);
-        const V3<R> ym = LdsPlane<R>::get(L, x.W, x.w[j] - x.hx);
-        const V3<R> yp = LdsPlane<R>::get(L, x.W, x.w[j] + x.hx);
+        const V3<R> ym = LdsPlane<R>::get(L, x.W, x.w[j] - x.tx);
+        const V3<R> yp = LdsPlane<R>::get(L, x.W, x.w[j] + x.tx);
         const V3<R> o0 = LdsPlane<R>::get(L, x.W, x.w[j]);
-        const V3<R> xm = p ? o0 : xd;
-        const V3<R> xp = p ? xd : o0;
         const uint32_t k = x.voff[j] / (uint32_t)sizeof(R) + x.P * z;
-        V3<R> nb;
-        if (MASK) {
-            // bonds cut by the site's mask (intergrain bonds) weigh zero
-            const uint32_t mb = mc[j];
-            const R w0 = (mb & 1u) ? R(1) : R(0), w1 = (mb & 2u) ? R(1) : R(0);
-            const R w2 = (mb & 4u) ? R(1) : R(0), w3 = (mb & 8u) ? R(1) : R(0);
-            const R w4 = (mb & 16u) ? R(1) : R(0), w5 = (mb & 32u) ? R(1) : R(0);
-            nb = V3<R>{((((w0 * xm.x + w1 * xp.x) + w2 * ym.x) + w3 * yp.x) + w4 * om[j].x) + w5 * op[j].x,
-                       ((((w0 * xm.y + w1 * xp.y) + w2 * ym.y) + w3 * yp.y) + w4 * om[j].y) + w5 * op[j].y,
-                       ((((w0 * xm.z + w1 * xp.z) + w2 * ym.z) + w3 * yp.z) + w4 * om[j].z) + w5 * op[j].z};
-        } else {
-            nb = V3<R>{((((xm.x + xp.x) + ym.x) + yp.x) + om[j].x) + op[j].x,
-                       ((((xm.y + xp.y) + ym.y) + yp.y) + om[j].y) + op[j].y,
-                       ((((xm.z + xp.z) + ym.z) + yp.z) + om[j].z) + op[j].z};
-        }
+        const V3<R> nb = neighbour_sum<R, MASK>(o0, xd, p, ym, yp, om[j], op[j], MASK ? mc[j] : 0u);
         const Rand4 rn = philox(x.sweep, 2u * k + p, (uint32_t)C, a.inst, a.key0, a.key1);
         const V3<R> f = update_site<R, OBS>(a.m, sc[j], nb, o0, rn, x.c1, x.scale, nacc, acc);
         g.put(C, x.voff[j], fz, f);
@@ -1014,15 +1026,15 @@ __device__ __forceinline__ void step2(const KArgs<R>& a, const Arrays<R>& g, con
     __syncthreads();
 }
 
-template <typename R, int C, bool OBS, int SPT, int HALO, bool MASK>
-__device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, HALO>& x,
-                                       uint32_t& nacc, Acc& acc)
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK>
+__device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, GEO>& x, uint32_t& nacc,
+                                       Acc& acc)
 {
     constexpr int O = 1 - C;
     // register planes: the other colour's z-1 (om) and three rotating slots
     // (planes z+1, z+2, z+3 at step z), the own colour's and the halo's
     // three rotating slots, and the masks'
-    V3<R> om[SPT], oA[SPT], oB[SPT], oC[SPT], sA[SPT], sB[SPT], sC[SPT], hA[HALO], hB[HALO], hC[HALO];
+    V3<R> om[SPT], oA[SPT], oB[SPT], oC[SPT], sA[SPT], sB[SPT], sC[SPT], hA[kHaloSlots<GEO>], hB[kHaloSlots<GEO>], hC[kHaloSlots<GEO>];
     uint32_t mA[SPT], mB[SPT], mC[SPT];
     {
         auto plane_off = [&](int zz) -> uint32_t {
@@ -1039,7 +1051,7 @@ __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, co
         // waits for every other prologue load, so no prologue load is still
         // in flight when the march starts and the waits inside the march are
         // set by the march alone
-        V3<R> o0[SPT], h0[HALO];
+        V3<R> o0[SPT], h0[kHaloSlots<GEO>];
 #pragma unroll
         for (int j = 0; j < SPT; ++j) {
             om[j] = g.get(O, x.voff[j], fm);
@@ -1053,16 +1065,16 @@ __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, co
             }
         }
 #pragma unroll
-        for (int i = 0; i < HALO; ++i) {
-            hA[i] = g.get(O, x.hvoff[i], f1);
-            hB[i] = g.get(O, x.hvoff[i], f2);
+        for (int i = 0; i < x.NH; ++i) {
+            hA[i] = g.get(O, x.halo(i, 1), f1);
+            hB[i] = g.get(O, x.halo(i, 0), f2);
         }
 #pragma unroll
         for (int j = 0; j < SPT; ++j) o0[j] = g.get(O, x.voff[j], f0);
 #pragma unroll
-        for (int i = 0; i < HALO; ++i) h0[i] = g.get(O, x.hvoff[i], f0);
+        for (int i = 0; i < x.NH; ++i) h0[i] = g.get(O, x.halo(i, 0), f0);
 #pragma unroll
-        for (int i = 0; i < HALO; ++i)
+        for (int i = 0; i < x.NH; ++i)
             if (x.hact[i]) LdsPlane<R>::put(x.lds[0], x.W, x.hw[i], h0[i]);
 #pragma unroll
         for (int j = 0; j < SPT; ++j) LdsPlane<R>::put(x.lds[0], x.W, x.w[j], o0[j]);
@@ -1084,33 +1096,32 @@ __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, co
     auto& pa = site_acc<R>(acc, part);
     uint32_t zi = 0;
     for (; zi + 3 <= x.zn; zi += 3) {
-        step2<R, C, OBS, SPT, HALO, MASK>(a, g, x, zi + 0, om, oA, oC, sA, sC, hA, hC, mA, mC, nacc, pa);
-        step2<R, C, OBS, SPT, HALO, MASK>(a, g, x, zi + 1, om, oB, oA, sB, sA, hB, hA, mB, mA, nacc, pa);
-        step2<R, C, OBS, SPT, HALO, MASK>(a, g, x, zi + 2, om, oC, oB, sC, sB, hC, hB, mC, mB, nacc, pa);
+        step2<R, C, OBS, SPT, GEO, MASK>(a, g, x, zi + 0, om, oA, oC, sA, sC, hA, hC, mA, mC, nacc, pa);
+        step2<R, C, OBS, SPT, GEO, MASK>(a, g, x, zi + 1, om, oB, oA, sB, sA, hB, hA, mB, mA, nacc, pa);
+        step2<R, C, OBS, SPT, GEO, MASK>(a, g, x, zi + 2, om, oC, oB, sC, sB, hC, hB, mC, mB, nacc, pa);
     }
-    if (zi < x.zn) step2<R, C, OBS, SPT, HALO, MASK>(a, g, x, zi + 0, om, oA, oC, sA, sC, hA, hC, mA, mC, nacc, pa);
-    if (zi + 1 < x.zn) step2<R, C, OBS, SPT, HALO, MASK>(a, g, x, zi + 1, om, oB, oA, sB, sA, hB, hA, mB, mA, nacc, pa);
+    if (zi < x.zn) step2<R, C, OBS, SPT, GEO, MASK>(a, g, x, zi + 0, om, oA, oC, sA, sC, hA, hC, mA, mC, nacc, pa);
+    if (zi + 1 < x.zn) step2<R, C, OBS, SPT, GEO, MASK>(a, g, x, zi + 1, om, oB, oA, sB, sA, hB, hA, mB, mA, nacc, pa);
     if constexpr (OBS) flush_part(acc, pa);
 
 }
 
-// One work-group of a colour pass: logical tile b (column block b % nqb,
-// z-slab b / nqb) of the lattice described by a, with the march of depth
-// two when DEEP.
-template <typename R, int C, bool OBS, int SPT, int HALO, bool MASK, bool DEEP>
-__device__ __forceinline__ void pass_tile(const KArgs<R>& a, const uint32_t zc, const uint32_t nqb, const uint32_t b,
+// One work-group of a colour pass: logical tile b (in-plane window or tile
+// b % n, of z-slab b / n) of the lattice described by a, with the march of
+// depth two when DEEP.
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, bool DEEP>
+__device__ __forceinline__ void pass_tile(const KArgs<R>& a, const PassGeom& q, const uint32_t zc, const uint32_t b,
                                           const R scale, unsigned char* smem)
 {
-    constexpr uint32_t Q = kThreads * SPT;
     const Arrays<R> g(a);
-    PassCtx<R, SPT, HALO> x;
-    x.hx = a.hx;
+    const uint32_t hx = a.hx, ny = a.ny;
+    PassCtx<R, SPT, GEO> x;
     x.P = a.P;
     x.nz = a.nz;
-    x.W = Q + 2u * a.hx;
+    x.tx = GEO == 0 ? q.tx : hx;
+    x.W = GEO == 0 ? q.entries : kThreads * SPT + 2u * hx;
     const uint32_t t = threadIdx.x;
-    const uint32_t qb = b % nqb, zb = b / nqb;
-    const uint32_t base = qb * Q;
+    const uint32_t zb = b / q.n, r = b - zb * q.n;
     x.z0 = zb * zc;
     x.zn = min(zc, a.nz - x.z0);
     x.lds[0] = smem;
@@ -1119,102 +1130,142 @@ __device__ __forceinline__ void pass_tile(const KArgs<R>& a, const uint32_t zc, 
     x.sweep = (uint32_t)a.st->sweep;
     x.scale = scale;
     x.zbound = a.zbound;
-
+    if constexpr (GEO != 0) {
+        constexpr uint32_t Q = kThreads * SPT;
+        const uint32_t base = r * Q;
 #pragma unroll
-    for (int j = 0; j < SPT; ++j) {
-        const uint32_t q = base + t + kThreads * j;
-        x.act[j] = q < a.P;
-        const uint32_t qm = x.act[j] ? q : q % a.P;
-        const uint32_t kx = qm % a.hx, yy = qm / a.hx;
-        x.voff[j] = qm * (uint32_t)sizeof(R);
-        x.w[j] = a.hx + t + kThreads * j;
-        x.par[j] = (yy + x.z0 + (uint32_t)C) & 1u;
-        // window entry of the x-neighbour that is not the same-index partner:
-        // x+1 (wrapping inside the row) when the site's x is odd, else x-1
+        for (int j = 0; j < SPT; ++j) {
+            const uint32_t k = base + t + (uint32_t)kThreads * j;
+            x.act[j] = k < a.P;
+            const uint32_t km = x.act[j] ? k : k % a.P;
+            const uint32_t kx = km % hx, yy = km / hx;
+            x.voff[j] = km * (uint32_t)sizeof(R);
+            x.w[j] = hx + t + (uint32_t)kThreads * j;
+            x.par[j] = (yy + x.z0 + (uint32_t)C) & 1u;
+            // window entry of the x-neighbour that is not the same-index partner:
+            // x+1 (wrapping inside the row) when the site's x is odd, else x-1
 #pragma unroll
-        for (int bpar = 0; bpar < 2; ++bpar) {
-            const uint32_t p = x.par[j] ^ (uint32_t)bpar;
-            const uint32_t w = x.w[j];
-            x.wd[bpar][j] = p ? (kx == a.hx - 1 ? w + 1 - a.hx : w + 1) : (kx == 0 ? w + a.hx - 1 : w - 1);
+            for (int bpar = 0; bpar < 2; ++bpar) {
+                const uint32_t p = x.par[j] ^ (uint32_t)bpar;
+                const uint32_t w = x.w[j];
+                x.wd[bpar][j] = p ? (kx == hx - 1 ? w + 1 - hx : w + 1) : (kx == 0 ? w + hx - 1 : w - 1);
+            }
         }
-    }
-    const uint32_t nh = 2u * a.hx;
 #pragma unroll
-    for (int i = 0; i < HALO; ++i) {
-        const uint32_t slot = t + kThreads * i;
-        x.hact[i] = slot < nh;
-        x.hw[i] = slot < a.hx ? slot : slot + Q;
-        x.hvoff[i] = ((base + x.hw[i] + a.P - a.hx) % a.P) * (uint32_t)sizeof(R);
+        for (int i = 0; i < x.NH; ++i) {
+            const uint32_t slot = t + (uint32_t)kThreads * i;
+            x.hact[i] = slot < 2u * hx;
+            x.hw[i] = slot < hx ? slot : slot + Q;
+            x.hvoff[i] = ((base + x.hw[i] + a.P - hx) % a.P) * (uint32_t)sizeof(R);
+        }
+        x.hodd = 0u;
+    } else {
+        const uint32_t by = r / q.ntx, bx = r - by * q.ntx;
+        const uint32_t x0 = bx * q.tx, y0 = by * q.ty;
+        const uint32_t tw = min(q.tx, hx - x0), th = min(q.ty, ny - y0);     // of this tile
+        const uint32_t edge = (q.ty + 2u) * q.tx;                            // entries of the sites beyond the edges
+#pragma unroll
+        for (int j = 0; j < SPT; ++j) {
+            const uint32_t e = t + (uint32_t)kThreads * j;
+            const uint32_t ly = e / q.tx, lx = e - ly * q.tx;
+            x.act[j] = lx < tw && ly < th;
+            const uint32_t cx = x.act[j] ? lx : 0u, cy = x.act[j] ? ly : 0u;
+            x.voff[j] = (x0 + cx + hx * (y0 + cy)) * (uint32_t)sizeof(R);
+            // a thread without a site writes its plane values to a spare entry
+            const uint32_t w = (cy + 1u) * q.tx + cx;
+            x.w[j] = x.act[j] ? w : q.entries - 1u;
+            x.par[j] = (y0 + cy + x.z0 + (uint32_t)C) & 1u;
+#pragma unroll
+            for (int bpar = 0; bpar < 2; ++bpar) {
+                const uint32_t p = x.par[j] ^ (uint32_t)bpar;
+                x.wd[bpar][j] = p ? (cx == tw - 1 ? edge + cy : w + 1) : (cx == 0 ? edge + cy : w - 1);
+            }
+        }
+        // halo slots: the row above, the row below, then the sites beyond the edges
+        const bool top = t < q.tx, row = t < 2u * q.tx;
+        const uint32_t lx = top ? t : t - q.tx, le = t - 2u * q.tx;
+        x.hact[0] = row ? lx < tw : le < th;
+        const uint32_t yy = top ? (y0 == 0 ? ny - 1 : y0 - 1) : (y0 + th == ny ? 0u : y0 + th);
+        uint32_t h[2];
+#pragma unroll
+        for (uint32_t bpar = 0; bpar < 2; ++bpar) {
+            // an odd site's neighbour lies right of the tile, an even one's left
+            const uint32_t p = (y0 + le + x.z0 + (uint32_t)C + bpar) & 1u;
+            const uint32_t xe = p ? (x0 + tw == hx ? 0u : x0 + tw) : (x0 == 0 ? hx - 1 : x0 - 1);
+            const uint32_t site = row ? x0 + lx + hx * yy : xe + hx * (y0 + le);
+            h[bpar] = x.hact[0] ? site * (uint32_t)sizeof(R) : 0u;
+        }
+        x.hvoff[0] = h[0];
+        x.hodd = h[1];
+        x.hw[0] = row ? (top ? lx : (th + 1u) * q.tx + lx) : edge + le;
     }
 
     uint32_t nacc = 0;
     Acc acc;
-    if constexpr (DEEP) march2<R, C, OBS, SPT, HALO, MASK>(a, g, x, nacc, acc);
-    else march1<R, C, OBS, SPT, HALO, MASK>(a, g, x, nacc, acc);
+    if constexpr (DEEP) march2<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc);
+    else march1<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc);
     // LDS is free after the last barrier of the march
     block_end<R, OBS, false>(a, C, b, nacc, acc, reinterpret_cast<double*>(smem));
 }
 
 // The depth-two FP32 variants with up to two sites per thread are held to
 // 128 registers (four waves per SIMD), which they reach without spilling.
-template <typename R, int SPT, int HALO, bool DEEP>
+template <typename R, int SPT, bool DEEP>
 constexpr int pass_waves_per_eu()
 {
-    return DEEP && sizeof(R) == 4 && (SPT == 1 || (SPT == 2 && HALO <= 2)) ? 4 : 1;
+    return DEEP && sizeof(R) == 4 && SPT <= 2 ? 4 : 1;
 }
 
-template <typename R, int C, bool OBS, int SPT, int HALO, bool MASK, bool DEEP>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, SPT, HALO, DEEP>())))
-void pass_kernel(const KArgs<R> a, const uint32_t zc, const uint32_t nqb, const uint32_t nblk, const R scale)
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, bool DEEP>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, SPT, DEEP>())))
+void pass_kernel(const KArgs<R> a, const PassGeom q, const uint32_t zc, const uint32_t nblk, const R scale)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    pass_tile<R, C, OBS, SPT, HALO, MASK, DEEP>(a, zc, nqb, xcd_remap(blockIdx.x, nblk), scale, smem);
+    pass_tile<R, C, OBS, SPT, GEO, MASK, DEEP>(a, q, zc, xcd_remap(blockIdx.x, nblk), scale, smem);
 }
 
 
 // Launch of one colour pass of one lattice; the kernel variant follows the
-// launch shape (sites per thread), the halo width and the colour.  Each
-// translation unit instantiates one family: the plain depth-one march in
-// hmc_kernels.hip, the masked one in hmc_masked_kernels.hip, the depth-two
-// march in hmc_deep_kernels.hip (so they compile in parallel).
+// launch shape (sites per thread), the geometry and the colour.  Each
+// translation unit instantiates one family: the plain depth-one march in hmc_kernels.hip, the
+// masked one in hmc_masked_kernels.hip, the depth-two march in
+// hmc_deep_kernels.hip (so they compile in parallel).
 template <bool MASK, bool DEEP>
 struct PassLaunch {
-    template <typename R, int C, bool OBS, int SPT, int HALO>
+    template <typename R, int C, bool OBS, int SPT, int GEO>
     static void go(const KArgs<R>& a, const DevLattice& d, int zc, double T, hipStream_t s)
     {
-        const uint32_t nqb = cdiv((uint64_t)d.P, (uint64_t)kThreads * SPT);
-        const uint32_t nzb = cdiv((uint64_t)d.nz, (uint64_t)zc);
-        const uint32_t nblk = nqb * nzb;
-        pass_kernel<R, C, OBS, SPT, HALO, MASK, DEEP><<<nblk, kThreads, pass_lds_bytes(d.precision, d.hx, SPT), s>>>(
-            a, (uint32_t)zc, nqb, nblk, Prim<R>::scale_for(T));
+        const uint32_t nblk = (uint32_t)pass_blocks(d, SPT, zc);
+        pass_kernel<R, C, OBS, SPT, GEO, MASK, DEEP><<<nblk, kThreads, pass_lds_bytes(d, SPT), s>>>(
+            a, pass_geom(d, SPT), (uint32_t)zc, nblk, Prim<R>::scale_for(T));
     }
 
-    template <typename R, int SPT, int HALO>
+    template <typename R, int SPT, int GEO>
     static void by_colour(const KArgs<R>& a, const DevLattice& d, int colour, bool obs, int zc, double T,
                           hipStream_t s)
     {
-        if (colour == 0) go<R, 0, false, SPT, HALO>(a, d, zc, T, s);
-        else if (obs) go<R, 1, true, SPT, HALO>(a, d, zc, T, s);
-        else go<R, 1, false, SPT, HALO>(a, d, zc, T, s);
+        if (colour == 0) go<R, 0, false, SPT, GEO>(a, d, zc, T, s);
+        else if (obs) go<R, 1, true, SPT, GEO>(a, d, zc, T, s);
+        else go<R, 1, false, SPT, GEO>(a, d, zc, T, s);
     }
 
     template <typename R, int SPT>
-    static void by_halo(const KArgs<R>& a, const DevLattice& d, int colour, bool obs, int zc, double T,
-                        hipStream_t s)
+    static void by_geometry(const KArgs<R>& a, const DevLattice& d, int colour, bool obs, int zc, double T,
+                            hipStream_t s)
     {
-        const int halo = halo_slots(d.hx);
-        if (halo == 1) by_colour<R, SPT, 1>(a, d, colour, obs, zc, T, s);
-        else if (halo == 2) by_colour<R, SPT, 2>(a, d, colour, obs, zc, T, s);
-        else by_colour<R, SPT, 4>(a, d, colour, obs, zc, T, s);
+        const int geo = geometry_of(d.hx);
+        if (geo == 1) by_colour<R, SPT, 1>(a, d, colour, obs, zc, T, s);
+        else if (geo == 2) by_colour<R, SPT, 2>(a, d, colour, obs, zc, T, s);
+        else by_colour<R, SPT, 0>(a, d, colour, obs, zc, T, s);
     }
 
     template <typename R>
     static void by_shape(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s)
     {
         const auto a = make_args<R>(d);
-        if (spt == 1) by_halo<R, 1>(a, d, colour, obs, zc, T, s);
-        else if (spt == 2) by_halo<R, 2>(a, d, colour, obs, zc, T, s);
-        else by_halo<R, 4>(a, d, colour, obs, zc, T, s);
+        if (spt == 1) by_geometry<R, 1>(a, d, colour, obs, zc, T, s);
+        else if (spt == 2) by_geometry<R, 2>(a, d, colour, obs, zc, T, s);
+        else by_geometry<R, 4>(a, d, colour, obs, zc, T, s);
     }
 
     static hipError_t run(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s)

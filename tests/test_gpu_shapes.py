@@ -116,3 +116,56 @@ def test_spins_in_site_order(H, shape, precision):
     x, y, z = (i.T.reshape(-1) for i in np.indices(shape))
     for c in (0, 1):
         assert np.array_equal(raw[3 * c:3 * c + 3].T, want[(x + y + z) % 2 == c], equal_nan=True)
+
+
+# rows above 256 colour sites (tiles): just above, a prime width, the widest; rows
+# that a tile's height does not divide, one row of tiles, thin and thick slabs
+@pytest.mark.parametrize("nx,ny,nz,boundary", [(514, 4, 2, "periodic"), (526, 18, 4, "antiperiodic"),
+                                               (1024, 2, 6, "periodic"), (1024, 46, 5, "open"), (640, 34, 3, "open")])
+@pytest.mark.parametrize("masked", [False, True])
+def test_tiles_match_reference(H, nx, ny, nz, boundary, masked):
+    from oracle import oracle as O
+    from tests import inputs
+    kw = dict(inputs.random_params(nx), seed=31, instance=4)
+    S = inputs.random_unit_spins(nx * ny * nz, 12)
+    o = O.OracleLattice(nx, ny, nz, boundary_z=boundary, **kw)
+    m = inputs.random_bond_masks((nx, ny, nz), 0.3, 5)
+    if masked:
+        o.set_bond_masks(m)
+    o.set_spins(S)
+    accepted = [o.sweep(0.8, sample=True) for _ in range(3)][-1]
+    ref = o.observables(0.8)
+    for spt, zc, depth in [(1, 1, 1), (2, 3, 1), (4, 16, 1)] + ([] if masked else [(1, 2, 2), (2, 4, 2)]):
+        g = H.Lattice(nx, ny, nz, precision=64, boundary_z=boundary, bond_masks=masked, **kw)
+        if masked:
+            g.set_bond_masks(m)
+        g.set_spins(S)
+        if 2 * (256 * spt + nx) * 24 > 65536:       # refused, as ever: the line of whole rows in LDS
+            with pytest.raises(H.HmcError):
+                g.set_launch(spt, zc)
+            continue
+        g.set_launch(spt, zc)
+        g.set_prefetch(depth)
+        g.sweep(0.8, 3, sample=True)
+        assert np.max(np.abs(g.spins() - o.spins())) <= 1e-12, (spt, zc, depth)
+        a = g.observables()
+        assert a["accepted_last"] == accepted and a["theta_deg"] == ref["theta_deg"]
+        for k in ("mean_m", "mean_E"):
+            assert np.allclose(a[k], ref[k], rtol=1e-11, atol=1e-13), k
+
+
+def test_tiles_in_a_batch_equal_tiles_alone(H):
+    kw = dict(precision=32, J=1.0, Ku=0.02, Kc=0.01, seed=9, init="random")
+    shapes = [((520, 6, 4), (4, 2)), ((1024, 10, 2), (1, 1)), ((12, 8, 6), (2, 3)), ((400, 6, 4), (1, 3))]
+    alone, inb = ([H.Lattice(*sh, instance=i, **kw) for i, (sh, _) in enumerate(shapes)] for _ in range(2))
+    for lats in (alone, inb):
+        for g, (_, c) in zip(lats, shapes):
+            g.set_launch(*c)
+    B = H.Batch(inb)
+    for n, smp in [(3, False), (4, True)]:
+        B.sweep(0.8, n, sample=smp)
+        for g in alone:
+            g.sweep(0.8, n, sample=smp)
+    for a, b in zip(alone, inb):
+        assert a.get_state() == b.get_state()
+    B.close()
