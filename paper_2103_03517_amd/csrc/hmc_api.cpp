@@ -362,19 +362,21 @@ int hmc_sweep(hmc_lattice* L, double T, int32_t n_sweeps, int32_t sample)
         if (st == HMC_OK) L->m_valid = obs;
         return st;
     }
+    const int fin = hmc::kFinCounts | (obs ? (hmc::kFinObs | hmc::kFinSample) : 0);
+    const bool carried = n_sweeps > 1 && hmc::pass_carries(L->d, L->spt, L->zc);
     for (int32_t it = 0; it < n_sweeps; ++it) {
+        const hmc::SweepCarry c{carried, it, fin};
         int64_t nr = 0, nb = 0;
         int st = launch(L, 0, "red pass", [&] {
-            return hmc::launch_pass(L->d, 0, false, L->spt, L->zc, T, L->stream, &nr);
+            return hmc::launch_pass(L->d, 0, false, L->spt, L->zc, T, c, L->stream, &nr);
         });
         if (st == HMC_OK)
             st = launch(L, 0, "black pass", [&] {
-                return hmc::launch_pass(L->d, 1, obs, L->spt, L->zc, T, L->stream, &nb);
+                return hmc::launch_pass(L->d, 1, obs, L->spt, L->zc, T, c, L->stream, &nb);
             });
-        if (st == HMC_OK)
+        if (st == HMC_OK && (!carried || it + 1 == n_sweeps))
             st = launch(L, 2, "finalize kernel", [&] {
-                const int fin = hmc::kFinCounts | (obs ? (hmc::kFinObs | hmc::kFinSample) : 0);
-                return hmc::launch_finalize(L->d, nr, nb, obs ? nb : 0, fin, T, L->stream);
+                return hmc::launch_finalize(L->d, nr, nb, obs ? nb : 0, fin, T, L->stream, carried ? it : 0);
             });
         if (st != HMC_OK) return st;
         L->m_valid = obs;

@@ -16,11 +16,10 @@ __global__ __launch_bounds__(kThreads) void finalize_batch_kernel(const BatchEnt
                                                                   const int32_t* __restrict__ fin)
 {
     __shared__ double scratch[kFinScratch];
-    __shared__ DevState sst;
     const BatchEntry<R>& E = tab[blockIdx.x];
     const int f = fin[blockIdx.x];
-    finalize_body<kThreads>(E.a.st, E.a.part, E.a.cnt_stride, E.a.cnt, E.nblk, E.nblk,
-                            (f & kFinObs) ? E.nblk : 0u, nullptr, f, T[blockIdx.x], E.N, scratch, &sst);
+    finalize_body<kThreads>(E.a.st, E.a.part, E.a.cnt_stride, E.a.cnt, E.a.cnt + E.a.cnt_stride, E.nblk, E.nblk,
+                            (f & kFinObs) ? E.nblk : 0u, nullptr, f, T[blockIdx.x], E.N, scratch);
 }
 
 // Clears the accumulators of every lattice of a batch (work-group i, lattice
@@ -74,11 +73,10 @@ __global__ __launch_bounds__(kThreads) void finalize_measure_batch_kernel(const 
                                                                           DevState* out)
 {
     __shared__ double scratch[kFinScratch];
-    __shared__ DevState sst;
     const uint32_t i = blockIdx.x;
     const BatchEntry<R>& E = tab[i];
-    finalize_body<kThreads>(E.a.st, E.a.part, E.a.cnt_stride, E.a.cnt, 0u, 0u, start[i + 1] - start[i], nullptr,
-                            kFinObs | kFinTorque, 0.0, E.N, scratch, &sst);
+    finalize_body<kThreads>(E.a.st, E.a.part, E.a.cnt_stride, E.a.cnt, E.a.cnt + E.a.cnt_stride, 0u, 0u, start[i + 1] - start[i], nullptr,
+                            kFinObs | kFinTorque, 0.0, E.N, scratch);
     __syncthreads();
     constexpr uint32_t words = sizeof(DevState) / 4;
     const uint32_t* src = reinterpret_cast<const uint32_t*>(E.a.st);
@@ -101,7 +99,7 @@ __global__ __launch_bounds__(kThreads) void pass_batch_kernel(const BatchEntry<R
     const uint32_t lo = owner_of(start, n, gb);
     const uint32_t e = ent[lo];
     const BatchEntry<R>& E = tab[e];
-    pass_tile<R, C, OBS, SPT, GEO, false, false>(E.a, E.geom, E.zc, gb - start[lo], scale[e], smem);
+    pass_tile<R, C, OBS, SPT, GEO, false, false>(E.a, E.geom, E.zc, gb - start[lo], scale[e], smem, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------

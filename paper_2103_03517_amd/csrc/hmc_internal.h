@@ -81,7 +81,8 @@ struct DevLattice {
     const void* c1tab;        // 181 reals: 1 - cos(theta) for theta in degrees
     void* aos;                // constrained sweeps: [colour][Nc] 4-vectors of the spins, then [Nc]
                               // records (spin, neighbour sum) of the colour being paired
-    double* part;             // [kNumPart][max_blocks]: work-group partials, one row per component
+    double* part;             // [kNumPart][max_blocks]: work-group partials, one row per component (the
+                              // last two rows hold what carried sweeps share)
     uint32_t* cnt;            // [2][max_blocks]
     int64_t max_blocks;
     double J, Ku, eu[3], Kc, h[3];
@@ -117,8 +118,19 @@ hipError_t launch_site_order(const DevLattice& d, double* xyz, bool in, hipStrea
 // Splits N bytes of bond masks in site order at src (device) into the
 // colour-split mask array of the lattice.
 hipError_t launch_split_masks(const DevLattice& d, const uint8_t* src, hipStream_t s);
-hipError_t launch_pass(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s,
-                       int64_t* blocks);
+// Sweeps of one call whose finalize the next red pass carries (pass_carries):
+// number `sweep` of the call, with the flags of its finalize.
+struct SweepCarry {
+    bool on;
+    int32_t sweep;
+    int32_t fin;
+};
+bool pass_carries(const DevLattice& d, int spt, int zc);
+uint32_t* red_counts(const DevLattice& d, int sweep);   // of a carried sweep, or (0) of any other launch
+struct PassSlot;
+PassSlot* carry_slots(const DevLattice& d);
+hipError_t launch_pass(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, const SweepCarry& c,
+                       hipStream_t s, int64_t* blocks);
 // Steps of a constrained call: copy the spins into the AoS working copy, the
 // neighbour sums of colour 0 or 1, the pair pass of colour 0 or 1, copy back.
 enum ConstrainedStep { kAosIn = 0, kNbRed, kPairRed, kNbBlack, kPairBlack, kAosOut };
@@ -140,9 +152,10 @@ int64_t measure_blocks(const DevLattice& d);
 // Mean spin of each z plane into out[3*nz] (device memory).
 hipError_t launch_plane_means(const DevLattice& d, double* out, hipStream_t s);
 // Reduces the counts of the colour-0 (red_blocks) and colour-1 (black_blocks)
-// launches and the partials of part_blocks work-groups into the state.
+// launches and the partials of part_blocks work-groups into the state (sweep:
+// the number of a carried sweep).
 hipError_t launch_finalize(const DevLattice& d, int64_t red_blocks, int64_t black_blocks, int64_t part_blocks,
-                           int fin, double T, hipStream_t s);
+                           int fin, double T, hipStream_t s, int sweep = 0);
 // Whole sweeps in one launch (hmc_sweep_kernels.hip): launch 0, 1, ... of a call
 // reads the spins and writes their copy in the constrained scratch (to_copy),
 // or the other way; launch_sweep_finalize closes the call's last one.

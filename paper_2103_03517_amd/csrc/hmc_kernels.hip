@@ -75,12 +75,11 @@ bool pass_shape_ok(int precision, int hx, int spt)
 // fold_groups_kernel in l2).  A lone work-group has no occupancy to gain, so
 // the register budget of four waves per SIMD goes to loads in flight.
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4)))
-void finalize_kernel(DevState* st, const double* part, uint32_t stride, const uint32_t* cnt, uint32_t nred,
-                     uint32_t nblack, uint32_t npart, const double* l2, int fin, double T, double N)
+void finalize_kernel(DevState* st, const double* part, uint32_t stride, const uint32_t* red, const uint32_t* black,
+                     uint32_t nred, uint32_t nblack, uint32_t npart, const double* l2, int fin, double T, double N)
 {
     __shared__ double scratch[kFinScratch];
-    __shared__ DevState sst;
-    finalize_body<1024>(st, part, stride, cnt, nred, nblack, npart, l2, fin, T, N, scratch, &sst);
+    finalize_body<1024>(st, part, stride, red, black, nred, nblack, npart, l2, fin, T, N, scratch);
 }
 
 // Work-group g: the sum S_g of record group g (the order of finalize_body),
@@ -322,10 +321,8 @@ __global__ __launch_bounds__(kThreads) void finalize_records_kernel(const KArgs<
     // the pair passes write at most 2 x HMC_PAIR_BLOCKS records: one group
     static_assert(2 * HMC_PAIR_BLOCKS <= kGroupRecords, "the fused finalize folds one group of records");
     __shared__ double scratch[kFinScratch];
-    __shared__ DevState sst;
     if (blockIdx.x == 0) {
-        finalize_body<kThreads>(a.st, a.part, a.cnt_stride, a.cnt, nrec, nrec, 2 * nrec, nullptr, fin, T, N, scratch,
-                                &sst);
+        finalize_body<kThreads>(a.st, a.part, a.cnt_stride, a.cnt, a.cnt + a.cnt_stride, nrec, nrec, 2 * nrec, nullptr, fin, T, N, scratch);
         return;
     }
     records_range<R, 0>(a, aos, rec, blockIdx.x - 1, gridDim.x - 1);
@@ -880,14 +877,35 @@ hipError_t launch_init(const DevLattice& d, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pass(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s,
-                       int64_t* blocks)
+hipError_t launch_pass(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, const SweepCarry& c,
+                       hipStream_t s, int64_t* blocks)
 {
     *blocks = pass_blocks(d, spt, zc);
     if (*blocks > d.max_blocks) return hipErrorInvalidValue;
-    if (d.mask) return launch_pass_masked(d, colour, obs, spt, zc, T, s);
-    if (pass_deep(d)) return launch_pass_deep(d, colour, obs, spt, zc, T, s);
-    return PassLaunch<false, false>::run(d, colour, obs, spt, zc, T, s);
+    if (d.mask) return launch_pass_masked(d, colour, obs, spt, zc, T, c, s);
+    if (pass_deep(d)) return launch_pass_deep(d, colour, obs, spt, zc, T, c, s);
+    return PassLaunch<false, false>::run(d, colour, obs, spt, zc, T, c, s);
+}
+
+// What carried sweeps share lies in the two rows of part that no record uses.
+uint32_t* red_counts(const DevLattice& d, int sweep)
+{
+    return sweep & 1 ? reinterpret_cast<uint32_t*>(d.part + (size_t)kTorqueRows * (size_t)d.max_blocks) : d.cnt;
+}
+
+PassSlot* carry_slots(const DevLattice& d)
+{
+    return reinterpret_cast<PassSlot*>(d.part + (size_t)(kTorqueRows + 1) * (size_t)d.max_blocks);
+}
+
+// Passes of up to 2048 records: there (masked 1024 x 1024 x 5, one site per thread)
+// a sweep still gains 3 us of 52 (MI355X).  In the default shapes more records
+// come with lattices whose sweeps take 440 us and more (384^3 FP32), of which a
+// finalize is 5, while every work-group would fold more counts.
+bool pass_carries(const DevLattice& d, int spt, int zc)
+{
+    return pass_blocks(d, spt, zc) <= kCarryRecords &&
+           2 * sizeof(PassSlot) <= (size_t)d.max_blocks * sizeof(double);
 }
 
 template <typename R>
@@ -1037,7 +1055,7 @@ hipError_t launch_measure(const DevLattice& d, hipStream_t s, int64_t* blocks)
 }
 
 hipError_t launch_finalize(const DevLattice& d, int64_t red_blocks, int64_t black_blocks, int64_t part_blocks,
-                           int fin, double T, hipStream_t s)
+                           int fin, double T, hipStream_t s, int sweep)
 {
     const uint32_t stride = (uint32_t)d.max_blocks;
     const uint32_t G = (uint32_t)cdiv((uint64_t)part_blocks, (uint64_t)kGroupRecords);
@@ -1049,8 +1067,9 @@ hipError_t launch_finalize(const DevLattice& d, int64_t red_blocks, int64_t blac
         fold_groups_kernel<<<G, kGroupThreads, 0, s>>>(d.part, stride, (uint32_t)part_blocks, nrows, g2);
         l2 = g2;
     }
-    finalize_kernel<<<1, 1024, 0, s>>>(d.st, d.part, stride, d.cnt, (uint32_t)red_blocks, (uint32_t)black_blocks,
-                                       (uint32_t)part_blocks, l2, fin, T, (double)d.N);
+    finalize_kernel<<<1, 1024, 0, s>>>(d.st, d.part, stride, red_counts(d, sweep), d.cnt + stride,
+                                       (uint32_t)red_blocks, (uint32_t)black_blocks, (uint32_t)part_blocks, l2, fin,
+                                       T, (double)d.N);
     return hipGetLastError();
 }
 

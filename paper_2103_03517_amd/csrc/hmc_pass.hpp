@@ -419,15 +419,82 @@ __device__ __forceinline__ void group_sums(const double* part, uint32_t stride, 
     __syncthreads();
 }
 
+// The old chain state, one value of each kind per lane of a wave: accumulator i
+// in lanes 0..4, that of the anisotropy energy in lane 5, of the torque in
+// lanes 7..9; and its update from the totals of a sweep or a measurement by that
+// wave.  Read early, it waits with the records' loads.  (One thread's chain of
+// loads, divisions and stores took 7000 cycles of a finalize: 13000 for 6000 in
+// the launch of a whole 16^3 sweep, MI355X.)
+struct StateLanes {
+    double shift, sum, sum2;
+    int64_t samples, torque_samples, sweep;
+    int32_t theta;
+    __device__ __forceinline__ void read(const DevState* st)
+    {
+        const uint32_t lane = threadIdx.x & 63u, i = min(lane, 4u);
+        shift = st->shift[i];
+        sum = lane == 5 ? st->sum_eanis : (lane >= 7 ? st->sum_torque[min(lane - 7u, 2u)] : st->sum[i]);
+        sum2 = st->sum2[i];
+        samples = st->samples;
+        torque_samples = st->torque_samples;
+        theta = st->theta;
+        sweep = st->sweep;
+    }
+    // tot: the totals of the NR folded rows; accepted: with kFinCounts
+    template <int NR>
+    __device__ __forceinline__ void update(DevState* st, const double* tot, long long accepted, int fin, double T,
+                                           double N) const
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        if ((fin & kFinCounts) && lane == 0) {
+            st->accepted_last = accepted;
+            if (2.0 * (double)accepted > N) st->theta = theta < 180 ? theta + 1 : theta;
+            else st->theta = theta > 1 ? theta - 1 : theta;
+            st->sweep = sweep + 1;
+        }
+        if (!(fin & kFinObs)) return;
+        const double row = tot[min(lane, (uint32_t)NR - 1u)];
+        if (__ballot(!isfinite(row)) && lane == 0) st->nonfinite = 1;
+        double* inst = st->M;                        // M[3], the four energies, the torque[3]
+        if (lane < (uint32_t)NR) inst[lane] = row;
+        if (!(fin & kFinSample)) return;
+        // lane 1, 2, 3: m_x, m_y, m_z; lane 4: E/N; lane 5: (E_uni + E_cub)/N; lanes
+        // 7..9: the torque; lane 0: |m|
+        double num = lane < 4 ? tot[lane == 0 ? 0u : lane - 1u] : row;
+        if (lane == 4) num = tot[kEexch] + tot[kEuni] + tot[kEcub] + tot[kEzee];
+        if (lane == 5) num = tot[kEuni] + tot[kEcub];
+        double x = num / N;
+        const double mx = read_lane(x, 1), my = read_lane(x, 2), mz = read_lane(x, 3);
+        const double ml = sqrt(mx * mx + my * my + mz * mz);
+        if (lane == 0) x = ml;
+        if (lane < 5) {
+            const double sh = samples == 0 ? x : shift, d = x - sh;
+            if (samples == 0) st->shift[lane] = x;
+            st->sum[lane] = sum + d;
+            st->sum2[lane] = sum2 + d * d;
+        } else if (lane == 5) {
+            st->sum_eanis = sum + x;
+        } else if (lane == 6) {
+            st->samples = samples + 1;
+            st->T_sample = T;
+            if (NR == kTorqueRows) st->torque_samples = torque_samples + 1;
+        } else if (NR == kTorqueRows && lane < 10) {
+            st->sum_torque[lane - 7u] = sum + x;
+        }
+    }
+};
+static_assert(offsetof(DevState, E_exch) == offsetof(DevState, M) + 24 && offsetof(DevState, E_zee) == offsetof(DevState, M) + 48 &&
+                  offsetof(DevState, torque) == offsetof(DevState, M) + 56,
+              "M, the energies and the torque lie in the order of the rows");
+
 // The finalize of one lattice by one work-group of NT threads (256 or 1024).
-// stride: row stride of part and cnt; l2: the group sums computed by
+// stride: row stride of part; red, black: the counts of the passes; l2: the group sums computed by
 // fold_groups_kernel ([G][kNumPart]), or null when this work-group computes
-// them.  sst: shared memory for a copy of the chain state, read at the start
-// so that the state update at the end does not wait for global memory.
+// them.
 template <int NT>
-__device__ __forceinline__ void finalize_body(DevState* st, const double* part, uint32_t stride, const uint32_t* cnt,
-                                              uint32_t nred, uint32_t nblack, uint32_t npart, const double* l2,
-                                              int fin, double T, double N, double* scratch, DevState* sst)
+__device__ __forceinline__ void finalize_body(DevState* st, const double* part, uint32_t stride,
+                                              const uint32_t* red, const uint32_t* black, uint32_t nred, uint32_t nblack, uint32_t npart, const double* l2,
+                                              int fin, double T, double N, double* scratch)
 {
     static_assert(NT >= kGroupThreads && NT % 64 == 0 && NT <= 1024, "work-group size");
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
@@ -435,9 +502,8 @@ __device__ __forceinline__ void finalize_body(DevState* st, const double* part, 
     double* sg = scratch + 16 * kNumPart;                                     // [4][kNumPart]
     double* tot = sg + 4 * kNumPart;                                          // [kNumPart + 1]
     unsigned long long* wc = reinterpret_cast<unsigned long long*>(tot + kNumPart + 1);   // [NT / 64]
-    // the last wave takes no part in the record fold: one of its threads
-    // copies the chain state while the others fold
-    if (t == (uint32_t)NT - 1) *sst = *st;
+    StateLanes old;
+    if (wave == 0) old.read(st);
     if (fin & kFinCounts) {
         // integer sums: any order gives the same total; eight loads in flight
         constexpr int UC = 8;
@@ -449,7 +515,7 @@ __device__ __forceinline__ void finalize_body(DevState* st, const double* part, 
             for (int u = 0; u < UC; ++u) {
                 const uint32_t j = i + (uint32_t)u * NT;
                 const uint32_t jj = j < nc ? j : i;                    // always in range
-                const uint32_t x = jj < nred ? cnt[jj] : cnt[stride + (jj - nred)];
+                const uint32_t x = jj < nred ? red[jj] : black[jj - nred];
                 w[u] = j < nc ? x : 0u;
             }
 #pragma unroll
@@ -483,66 +549,12 @@ __device__ __forceinline__ void finalize_body(DevState* st, const double* part, 
         }
     }
     __syncthreads();
-    if ((fin & kFinCounts) && t == (uint32_t)kNumPart) {
-        unsigned long long c = 0;
+    if (wave != 0) return;
+    unsigned long long c = 0;
+    if (fin & kFinCounts)
         for (int w = 0; w < NT / 64; ++w) c += wc[w];
-        tot[kNumPart] = (double)c;
-    }
-    __syncthreads();
-    if (t != 0) return;
-    const DevState& cur = *sst;
-    if (fin & kFinCounts) {
-        const long long accepted = (long long)tot[kNumPart];
-        st->accepted_last = accepted;
-        int32_t th = cur.theta;
-        if (2.0 * (double)accepted > N) {
-            if (th < 180) th += 1;
-        } else {
-            if (th > 1) th -= 1;
-        }
-        st->theta = th;
-        st->sweep = cur.sweep + 1;
-    }
-    if (fin & kFinObs) {
-        bool finite = true;
-        for (int i = 0; i < 10; ++i) finite = finite && isfinite(tot[i]);
-        if (!finite) st->nonfinite = 1;
-        st->M[0] = tot[kMx];
-        st->M[1] = tot[kMy];
-        st->M[2] = tot[kMz];
-        st->E_exch = tot[kEexch];
-        st->E_uni = tot[kEuni];
-        st->E_cub = tot[kEcub];
-        st->E_zee = tot[kEzee];
-        if (fin & kFinTorque) {
-            st->torque[0] = tot[kTx];
-            st->torque[1] = tot[kTy];
-            st->torque[2] = tot[kTz];
-        }
-        if (fin & kFinSample) {
-            double x[5];
-            x[1] = tot[kMx] / N;
-            x[2] = tot[kMy] / N;
-            x[3] = tot[kMz] / N;
-            x[0] = sqrt(x[1] * x[1] + x[2] * x[2] + x[3] * x[3]);
-            x[4] = (tot[kEexch] + tot[kEuni] + tot[kEcub] + tot[kEzee]) / N;
-            const bool first = cur.samples == 0;
-            for (int i = 0; i < 5; ++i) {
-                const double sh = first ? x[i] : cur.shift[i];
-                if (first) st->shift[i] = x[i];
-                const double d = x[i] - sh;
-                st->sum[i] = cur.sum[i] + d;
-                st->sum2[i] = cur.sum2[i] + d * d;
-            }
-            st->sum_eanis = cur.sum_eanis + (tot[kEuni] + tot[kEcub]) / N;
-            if (fin & kFinTorque) {
-                for (int i = 0; i < 3; ++i) st->sum_torque[i] = cur.sum_torque[i] + tot[kTx + i] / N;
-                st->torque_samples = cur.torque_samples + 1;
-            }
-            st->samples = cur.samples + 1;
-            st->T_sample = T;
-        }
-    }
+    if (fin & kFinTorque) old.update<kTorqueRows>(st, tot, (long long)c, fin, T, N);
+    else old.update<kObsRows>(st, tot, (long long)c, fin, T, N);
 }
 
 // ---------------------------------------------------------------------------
@@ -614,87 +626,189 @@ __device__ __forceinline__ void write_record(const double (&v)[NV], uint32_t nac
     }
 }
 
-// The finalize of a sweep from n records (rows of n partials and a row of
-// counts), by a work-group of NT threads: theta rule, sweep counter, and by the
-// flags the observables, the torque and the accumulators, as finalize_body.  A
-// wave folds a row; the state update runs across lanes, and its old values are
-// fetched with the records: in finalize_body's form, one thread's chain of
-// divisions and stores, this work-group took 13000 cycles where the tiles of
-// a 16^3 sweep took 9000 (MI355X).  tot: NR doubles and totc in shared memory.
-template <int NT, int NR>
-__device__ __forceinline__ void fold_sweep(DevState* st, const double* part, const uint32_t* cnt, uint32_t n, int fin,
-                                           double T, double N, double* tot, unsigned long long* totc)
+// The finalize of a sweep by a work-group of NT threads: theta rule, sweep
+// counter, and by the flags the observables, the torque and the accumulators.
+// A wave folds a row (row(e): its sum) or the counts (counts()).  tot: NR doubles
+// and totc in shared memory.
+template <int NT, int NR, typename Row, typename Counts>
+__device__ __forceinline__ void fold_sweep(DevState* st, int fin, double T, double N, double* tot,
+                                           unsigned long long* totc, Row row, Counts counts)
 {
     constexpr uint32_t NW = NT / 64;
     static_assert(NR == kObsRows || NR == kTorqueRows, "rows of a record");
     const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6;
-    // the old state, one value per lane of wave 0: accumulator i of lanes 0..4,
-    // that of the anisotropy energy in lane 5, of the torque in lanes 7..9
-    double shift = 0.0, sum = 0.0, sum2 = 0.0;
-    int32_t theta = 0;
-    int64_t samples = 0, torque_samples = 0, sweep = 0;
-    if (wave == 0) {
-        const uint32_t i = min(lane, 4u);
-        shift = st->shift[i];
-        sum = lane == 5 ? st->sum_eanis : (lane >= 7 ? st->sum_torque[min(lane - 7u, 2u)] : st->sum[i]);
-        sum2 = st->sum2[i];
-        samples = st->samples;
-        torque_samples = st->torque_samples;
-        theta = st->theta;
-        sweep = st->sweep;
-    }
-    for (uint32_t row = wave; row <= (uint32_t)NR; row += NW) {
-        if (row == (uint32_t)NR) {
-            const unsigned long long c = fold_counts(cnt, n);
+    StateLanes old;
+    if (wave == 0) old.read(st);
+    for (uint32_t e = wave; e <= (uint32_t)NR; e += NW) {
+        if (e == (uint32_t)NR) {
+            const unsigned long long c = counts();
             if (lane == 0) *totc = c;
         } else if (fin & kFinObs) {
-            const double x = fold_row(part, row, n);
-            if (lane == 0) tot[row] = x;
+            const double x = row(e);
+            if (lane == 0) tot[e] = x;
         }
     }
     __syncthreads();
-    if (wave != 0) return;
-    const long long accepted = (long long)*totc;
-    if (lane == 0) {
-        st->accepted_last = accepted;
-        if (2.0 * (double)accepted > N) theta = theta < 180 ? theta + 1 : theta;
-        else theta = theta > 1 ? theta - 1 : theta;
-        st->theta = theta;
-        st->sweep = sweep + 1;
-    }
-    if (!(fin & kFinObs)) return;
-    const double row = tot[min(lane, (uint32_t)NR - 1u)];
-    if (__ballot(!isfinite(row)) && lane == 0) st->nonfinite = 1;
-    double* inst = st->M;                        // M[3], the four energies, the torque[3]
-    if (lane < (uint32_t)NR) inst[lane] = row;
-    if (!(fin & kFinSample)) return;
-    // lane 1, 2, 3: m_x, m_y, m_z; lane 4: E/N; lane 5: (E_uni + E_cub)/N; lanes
-    // 7..9: the torque; lane 0: |m|
-    double num = lane < 4 ? tot[lane == 0 ? 0u : lane - 1u] : row;
-    if (lane == 4) num = tot[kEexch] + tot[kEuni] + tot[kEcub] + tot[kEzee];
-    if (lane == 5) num = tot[kEuni] + tot[kEcub];
-    double x = num / N;
-    const double mx = read_lane(x, 1), my = read_lane(x, 2), mz = read_lane(x, 3);
-    const double ml = sqrt(mx * mx + my * my + mz * mz);
-    if (lane == 0) x = ml;
-    if (lane < 5) {
-        const double sh = samples == 0 ? x : shift, d = x - sh;
-        if (samples == 0) st->shift[lane] = x;
-        st->sum[lane] = sum + d;
-        st->sum2[lane] = sum2 + d * d;
-    } else if (lane == 5) {
-        st->sum_eanis = sum + x;
-    } else if (lane == 6) {
-        st->samples = samples + 1;
-        st->T_sample = T;
-        if (NR == kTorqueRows) st->torque_samples = torque_samples + 1;
-    } else if (NR == kTorqueRows && lane < 10) {
-        st->sum_torque[lane - 7u] = sum + x;
-    }
+    if (wave == 0) old.update<NR>(st, tot, (long long)*totc, fin, T, N);
 }
-static_assert(offsetof(DevState, E_exch) == offsetof(DevState, M) + 24 && offsetof(DevState, E_zee) == offsetof(DevState, M) + 48 &&
-                  offsetof(DevState, torque) == offsetof(DevState, M) + 56,
-              "M, the energies and the torque lie in the order of the rows");
+
+// ... from n records: rows of n partials and a row of counts.
+template <int NT, int NR>
+__device__ __forceinline__ void fold_sweep(DevState* st, const double* part, const uint32_t* cnt, uint32_t n, int fin,
+                                           double T, double N, double* tot, unsigned long long* totc)
+{
+    fold_sweep<NT, NR>(st, fin, T, N, tot, totc, [&](uint32_t e) { return fold_row(part, e, n); },
+                       [&] { return fold_counts(cnt, n); });
+}
+
+// Records of a row through a buffer resource of its length: what lies past the
+// end reads as zero, which changes no sum.
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const T* p, uint32_t n)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, (int)(n * (uint32_t)sizeof(T)), kBufferConfig);
+}
+
+constexpr int kCarryRecords = 2048;
+
+// The total of the n records at p, by one wave: the order of finalize_body,
+// whose 256 threads a wave stands for in four steps.  (Eight loads in flight: the
+// pass this is part of has no registers for more.)
+__device__ __forceinline__ double fold_groups(const double* p, uint32_t n)
+{
+    const __amdgpu_buffer_rsrc_t r = row_rsrc(p, n);
+    const uint32_t lane = threadIdx.x & 63u;
+    double total = 0.0, sum = 0.0;
+#pragma unroll 1
+    for (uint32_t w0 = 0; w0 < 4u * ((n + kGroupRecords - 1u) / kGroupRecords); w0 += 2) {
+        const uint32_t v = (w0 / 4u) * (uint32_t)(8 * kGroupRecords) + (w0 % 4u) * 512u + lane * 8u;
+        double q[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) q[u] = Gm<double>::ld(r, v + (u >> 1) * 2048u + (u & 1u) * 512u, 0u);
+#pragma unroll
+        for (uint32_t w = 0; w < 2; ++w) {
+            double x = 0.0;
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) x += q[2u * u + w];
+            sum += wave_sum(x);
+        }
+        if (w0 % 4u == 2u) {
+            total += sum;
+            sum = 0.0;
+        }
+    }
+    return total;
+}
+
+// The counts of the n records of two passes, by one wave (at most one a spin, so
+// below 2^32).
+__device__ __forceinline__ uint32_t fold_pass_counts(const uint32_t* red, const uint32_t* black, uint32_t n)
+{
+    const __amdgpu_buffer_rsrc_t r = row_rsrc(red, n), b = row_rsrc(black, n);
+    const uint32_t v = (threadIdx.x & 63u) * 4u;
+    uint32_t c = 0;
+#pragma unroll 1
+    for (uint32_t u0 = 0; u0 * 64u < n; u0 += 8)
+#pragma unroll
+        for (uint32_t u = u0; u < u0 + 8; ++u)
+            c += __builtin_amdgcn_raw_buffer_load_b32(r, v + u * 256u, 0u, 0) +
+                 __builtin_amdgcn_raw_buffer_load_b32(b, v + u * 256u, 0u, 0);
+    return wave_sum(c);
+}
+
+// ---------------------------------------------------------------------------
+// Sweeps that follow each other in one call, where a pass leaves at most 2048
+// records: the red pass of the next sweep does what a finalize launch would.
+// Each of its work-groups sums the counts of the sweep before (its own next
+// cone angle; the loads pass behind those of the march's first planes), and one
+// work-group more runs the whole finalize meanwhile.  What the passes of a sweep
+// share goes through a slot; slots and the red counts are kept twice, by the
+// parity of the sweep in the call, so that no launch writes what its own
+// work-groups read.  Against a finalize launch per sweep (MI355X,
+// us a sampled sweep in the default shapes): FP32 96^3 20.5 -> 17.4, 128^3 27.1 ->
+// 24.6, 64 x 64 x 512 27.1 -> 24.3, 160^3 40.0 -> 36.0, 256^3 111.5 -> 108.3, masked
+// 1024 x 1024 x 5 52.0 -> 49.0; FP64 120 x 98 x 62 29.0 -> 24.7, 128^3 47 -> 44.
+// ---------------------------------------------------------------------------
+struct PassSlot {
+    int32_t theta;
+    uint32_t pad;
+    int64_t sweep;
+};
+static_assert(offsetof(PassSlot, theta) == offsetof(DevState, theta) && offsetof(PassSlot, sweep) == offsetof(DevState, sweep),
+              "a pass reads either");
+
+struct PassHead {
+    const PassSlot* from;    // what the sweep (red: the one before) left, or the chain state
+    PassSlot* to;            // red of a carried sweep: what it leaves; else null
+    const uint32_t* red;     // the counts of the sweep before
+    const uint32_t* black;
+    uint32_t nrec;           // of each: 0 where the pass takes the cone angle as it is
+    int32_t fin;             // finalize flags
+    double T, N;
+};
+
+// The head of a pass: cone angle and sweep number, from vector loads, which hold
+// up nothing before their use.  load() comes before the loads of the march's
+// first planes, table() after them, ready() stands for the barrier that follows.
+template <typename R, int C>
+struct HeadLoads {
+    static constexpr uint32_t NC = kCarryRecords / kThreads;
+    uint32_t c[2 * NC];
+    int32_t theta;
+    uint32_t sweep;
+    R c1, down;
+    __device__ __forceinline__ void load(const PassHead& h)
+    {
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(h.from, 1u);
+        theta = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (uint32_t)offsetof(PassSlot, theta), 0u, 0);
+        sweep = __builtin_amdgcn_raw_buffer_load_b32(rs, (uint32_t)offsetof(PassSlot, sweep), 0u, 0);
+        if constexpr (C == 0) {
+            const __amdgpu_buffer_rsrc_t r = row_rsrc(h.red, h.nrec), b = row_rsrc(h.black, h.nrec);
+#pragma unroll
+            for (uint32_t u = 0; u < NC; ++u) {
+                const uint32_t v = (u * (uint32_t)kThreads + threadIdx.x) * 4u;
+                c[2 * u] = c[2 * u + 1] = 0u;
+                if (u >= NC / 2 && h.nrec <= (uint32_t)kCarryRecords / 2u) continue;
+                c[2 * u] = __builtin_amdgcn_raw_buffer_load_b32(r, v, 0u, 0);
+                c[2 * u + 1] = __builtin_amdgcn_raw_buffer_load_b32(b, v, 0u, 0);
+            }
+        }
+    }
+    __device__ __forceinline__ void table(const KArgs<R>& a, const PassHead& h)
+    {
+        const __amdgpu_buffer_rsrc_t r = row_rsrc(a.c1tab, 181u);
+        if constexpr (C == 0) {
+            const int32_t up = h.nrec ? min(theta + 1, 180) : theta, dn = h.nrec ? max(theta - 1, 1) : theta;
+            c1 = Gm<R>::ld(r, (uint32_t)up * (uint32_t)sizeof(R), 0u);
+            down = Gm<R>::ld(r, (uint32_t)dn * (uint32_t)sizeof(R), 0u);
+        } else {
+            c1 = Gm<R>::ld(r, (uint32_t)theta * (uint32_t)sizeof(R), 0u);
+        }
+    }
+    __device__ __forceinline__ void ready(const PassHead& h, uint32_t* wtot)
+    {
+        if constexpr (C == 0) {
+            uint32_t n = 0;
+#pragma unroll
+            for (uint32_t u = 0; u < 2 * NC; ++u) n += c[u];
+            n = wave_sum(n);
+            if ((threadIdx.x & 63u) == 0) wtot[threadIdx.x >> 6] = n;
+        }
+        __syncthreads();
+        // the same on every lane: into scalar registers
+        theta = read_lane(theta, 0);
+        sweep = read_lane(sweep, 0);
+        if (C == 0 && h.nrec) {
+            long long accepted = 0;
+            for (int w = 0; w < kThreads / 64; ++w) accepted += (long long)wtot[w];
+            const bool more = 2.0 * (double)accepted > h.N;
+            theta = more ? min(theta + 1, 180) : max(theta - 1, 1);
+            ++sweep;
+            c1 = more ? c1 : down;
+        }
+        c1 = read_lane(c1, 0);
+    }
+};
 
 // ---------------------------------------------------------------------------
 // The Metropolis update of one site (Table A1, Eq. 1, Eq. 2): cone proposal,
@@ -889,9 +1003,12 @@ __device__ __forceinline__ void step1(const KArgs<R>& a, const Arrays<R>& g, con
     __syncthreads();
 }
 
-template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK>
+// table and ready: what is due after the loads of the first planes, and in place
+// of the barrier behind their stores (the cone angle and the sweep number are
+// read no earlier).
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, typename Table, typename Ready>
 __device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, GEO>& x, uint32_t& nacc,
-                                       Acc& acc)
+                                       Acc& acc, Table table, Ready ready)
 {
     constexpr int O = 1 - C;
     V3<R> rA[SPT], rB[SPT], rC[SPT], rD[SPT], s0[SPT], s1[SPT], h0[kHaloSlots<GEO>], h1[kHaloSlots<GEO>];
@@ -910,6 +1027,7 @@ __device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, co
             s0[j] = g.get(C, x.voff[j], f0);
             if (MASK) m0[j] = a.mask[C][x.voff[j] / (uint32_t)sizeof(R) + a.P * x.z0];
         }
+        table();
 #pragma unroll
         for (int i = 0; i < x.NH; ++i)
             if (x.hact[i]) {
@@ -930,7 +1048,7 @@ __device__ __forceinline__ void march1(const KArgs<R>& a, const Arrays<R>& g, co
             for (int j = 0; j < SPT; ++j) rC[j] = across_z(rC[j], x.zbound);
         }
     }
-    __syncthreads();
+    ready();
 
     Part<R> part;
     auto& pa = site_acc<R>(acc, part);
@@ -1026,9 +1144,9 @@ __device__ __forceinline__ void step2(const KArgs<R>& a, const Arrays<R>& g, con
     __syncthreads();
 }
 
-template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK>
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, typename Table, typename Ready>
 __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, const PassCtx<R, SPT, GEO>& x, uint32_t& nacc,
-                                       Acc& acc)
+                                       Acc& acc, Table table, Ready ready)
 {
     constexpr int O = 1 - C;
     // register planes: the other colour's z-1 (om) and three rotating slots
@@ -1073,6 +1191,7 @@ __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, co
         for (int j = 0; j < SPT; ++j) o0[j] = g.get(O, x.voff[j], f0);
 #pragma unroll
         for (int i = 0; i < x.NH; ++i) h0[i] = g.get(O, x.halo(i, 0), f0);
+        table();
 #pragma unroll
         for (int i = 0; i < x.NH; ++i)
             if (x.hact[i]) LdsPlane<R>::put(x.lds[0], x.W, x.hw[i], h0[i]);
@@ -1090,7 +1209,7 @@ __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, co
             }
         }
     }
-    __syncthreads();
+    ready();
 
     Part<R> part;
     auto& pa = site_acc<R>(acc, part);
@@ -1108,12 +1227,15 @@ __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, co
 
 // One work-group of a colour pass: logical tile b (in-plane window or tile
 // b % n, of z-slab b / n) of the lattice described by a, with the march of
-// depth two when DEEP.
+// depth two when DEEP.  head: null in a batch, whose passes read the chain
+// state; wtot: a word per wave in shared memory with it.
 template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, bool DEEP>
 __device__ __forceinline__ void pass_tile(const KArgs<R>& a, const PassGeom& q, const uint32_t zc, const uint32_t b,
-                                          const R scale, unsigned char* smem)
+                                          const R scale, unsigned char* smem, const PassHead* head, uint32_t* wtot)
 {
     const Arrays<R> g(a);
+    HeadLoads<R, C> hl;
+    if (head) hl.load(*head);
     const uint32_t hx = a.hx, ny = a.ny;
     PassCtx<R, SPT, GEO> x;
     x.P = a.P;
@@ -1126,8 +1248,10 @@ __device__ __forceinline__ void pass_tile(const KArgs<R>& a, const PassGeom& q, 
     x.zn = min(zc, a.nz - x.z0);
     x.lds[0] = smem;
     x.lds[1] = smem + (size_t)x.W * LdsPlane<R>::bytes_per_entry;
-    x.c1 = a.c1tab[a.st->theta];
-    x.sweep = (uint32_t)a.st->sweep;
+    if (!head) {
+        x.c1 = a.c1tab[a.st->theta];
+        x.sweep = (uint32_t)a.st->sweep;
+    }
     x.scale = scale;
     x.zbound = a.zbound;
     if constexpr (GEO != 0) {
@@ -1202,8 +1326,22 @@ __device__ __forceinline__ void pass_tile(const KArgs<R>& a, const PassGeom& q, 
 
     uint32_t nacc = 0;
     Acc acc;
-    if constexpr (DEEP) march2<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc);
-    else march1<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc);
+    const auto table = [&] {
+        if (head) hl.table(a, *head);
+    };
+    const auto ready = [&] {
+        if (!head) {
+            __syncthreads();
+            return;
+        }
+        hl.ready(*head, wtot);
+        x.c1 = hl.c1;
+        x.sweep = hl.sweep;
+    };
+    if constexpr (DEEP) march2<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc, table, ready);
+    else march1<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc, table, ready);
+    if (C == 0 && head && head->to && b == 0 && threadIdx.x == 0)
+        *head->to = PassSlot{hl.theta, 0u, (int64_t)hl.sweep};
     // LDS is free after the last barrier of the march
     block_end<R, OBS, false>(a, C, b, nacc, acc, reinterpret_cast<double*>(smem));
 }
@@ -1218,12 +1356,22 @@ constexpr int pass_waves_per_eu()
 
 template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, bool DEEP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, SPT, DEEP>())))
-void pass_kernel(const KArgs<R> a, const PassGeom q, const uint32_t zc, const uint32_t nblk, const R scale)
+void pass_kernel(const KArgs<R> a, const PassGeom q, const uint32_t zc, const uint32_t nblk, const R scale,
+                 const PassHead h)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    pass_tile<R, C, OBS, SPT, GEO, MASK, DEEP>(a, q, zc, xcd_remap(blockIdx.x, nblk), scale, smem);
+    __shared__ uint32_t wtot[kThreads / 64];
+    if (C == 0 && blockIdx.x == nblk) {
+        // (the records lie before the red counts this launch writes)
+        double* tot = reinterpret_cast<double*>(smem);
+        fold_sweep<kThreads, kObsRows>(
+            a.st, h.fin, h.T, h.N, tot, reinterpret_cast<unsigned long long*>(tot + kObsRows),
+            [&](uint32_t e) { return fold_groups(a.part + (size_t)e * a.cnt_stride, nblk); },
+            [&] { return fold_pass_counts(h.red, h.black, nblk); });
+        return;
+    }
+    pass_tile<R, C, OBS, SPT, GEO, MASK, DEEP>(a, q, zc, xcd_remap(blockIdx.x, nblk), scale, smem, &h, wtot);
 }
-
 
 // Launch of one colour pass of one lattice; the kernel variant follows the
 // launch shape (sites per thread), the geometry and the colour.  Each
@@ -1233,45 +1381,65 @@ void pass_kernel(const KArgs<R> a, const PassGeom q, const uint32_t zc, const ui
 template <bool MASK, bool DEEP>
 struct PassLaunch {
     template <typename R, int C, bool OBS, int SPT, int GEO>
-    static void go(const KArgs<R>& a, const DevLattice& d, int zc, double T, hipStream_t s)
+    static void go(const KArgs<R>& args, const DevLattice& d, int zc, double T, const SweepCarry& c, hipStream_t s)
     {
         const uint32_t nblk = (uint32_t)pass_blocks(d, SPT, zc);
-        pass_kernel<R, C, OBS, SPT, GEO, MASK, DEEP><<<nblk, kThreads, pass_lds_bytes(d, SPT), s>>>(
-            a, pass_geom(d, SPT), (uint32_t)zc, nblk, Prim<R>::scale_for(T));
+        KArgs<R> a = args;
+        PassSlot* slot = c.on ? carry_slots(d) : nullptr;
+        const bool head = c.on && C == 0 && c.sweep > 0;         // finalizes the sweep before
+        PassHead h{};
+        h.from = reinterpret_cast<const PassSlot*>(d.st);
+        if (head) h.from = slot + ((c.sweep - 1) & 1);
+        else if (c.on && C == 1) h.from = slot + (c.sweep & 1);
+        h.red = red_counts(d, c.sweep - 1);
+        h.black = d.cnt + d.max_blocks;
+        h.nrec = head ? nblk : 0u;
+        h.fin = c.fin;
+        h.T = T;
+        h.N = (double)d.N;
+        if (c.on && C == 0) {
+            h.to = slot + (c.sweep & 1);
+            a.cnt = red_counts(d, c.sweep);
+        }
+        const uint32_t grid = nblk + (head ? 1u : 0u);
+        pass_kernel<R, C, OBS, SPT, GEO, MASK, DEEP><<<grid, kThreads, pass_lds_bytes(d, SPT), s>>>(
+            a, pass_geom(d, SPT), (uint32_t)zc, nblk, Prim<R>::scale_for(T), h);
     }
 
     template <typename R, int SPT, int GEO>
     static void by_colour(const KArgs<R>& a, const DevLattice& d, int colour, bool obs, int zc, double T,
-                          hipStream_t s)
+                          const SweepCarry& c, hipStream_t s)
     {
-        if (colour == 0) go<R, 0, false, SPT, GEO>(a, d, zc, T, s);
-        else if (obs) go<R, 1, true, SPT, GEO>(a, d, zc, T, s);
-        else go<R, 1, false, SPT, GEO>(a, d, zc, T, s);
+        if (colour == 0) go<R, 0, false, SPT, GEO>(a, d, zc, T, c, s);
+        else if (obs) go<R, 1, true, SPT, GEO>(a, d, zc, T, c, s);
+        else go<R, 1, false, SPT, GEO>(a, d, zc, T, c, s);
     }
 
     template <typename R, int SPT>
     static void by_geometry(const KArgs<R>& a, const DevLattice& d, int colour, bool obs, int zc, double T,
-                            hipStream_t s)
+                            const SweepCarry& c, hipStream_t s)
     {
         const int geo = geometry_of(d.hx);
-        if (geo == 1) by_colour<R, SPT, 1>(a, d, colour, obs, zc, T, s);
-        else if (geo == 2) by_colour<R, SPT, 2>(a, d, colour, obs, zc, T, s);
-        else by_colour<R, SPT, 0>(a, d, colour, obs, zc, T, s);
+        if (geo == 1) by_colour<R, SPT, 1>(a, d, colour, obs, zc, T, c, s);
+        else if (geo == 2) by_colour<R, SPT, 2>(a, d, colour, obs, zc, T, c, s);
+        else by_colour<R, SPT, 0>(a, d, colour, obs, zc, T, c, s);
     }
 
     template <typename R>
-    static void by_shape(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s)
+    static void by_shape(const DevLattice& d, int colour, bool obs, int spt, int zc, double T,
+                         const SweepCarry& c, hipStream_t s)
     {
         const auto a = make_args<R>(d);
-        if (spt == 1) by_geometry<R, 1>(a, d, colour, obs, zc, T, s);
-        else if (spt == 2) by_geometry<R, 2>(a, d, colour, obs, zc, T, s);
-        else by_geometry<R, 4>(a, d, colour, obs, zc, T, s);
+        if (spt == 1) by_geometry<R, 1>(a, d, colour, obs, zc, T, c, s);
+        else if (spt == 2) by_geometry<R, 2>(a, d, colour, obs, zc, T, c, s);
+        else by_geometry<R, 4>(a, d, colour, obs, zc, T, c, s);
     }
 
-    static hipError_t run(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s)
+    static hipError_t run(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, const SweepCarry& c,
+                          hipStream_t s)
     {
-        if (d.precision == 32) by_shape<float>(d, colour, obs, spt, zc, T, s);
-        else by_shape<double>(d, colour, obs, spt, zc, T, s);
+        if (d.precision == 32) by_shape<float>(d, colour, obs, spt, zc, T, c, s);
+        else by_shape<double>(d, colour, obs, spt, zc, T, c, s);
         return hipGetLastError();
     }
 };
@@ -1360,8 +1528,10 @@ __device__ __forceinline__ void measure_column(const KArgs<R>& a, const uint32_t
 }
 
 // The colour pass of a lattice with bond masks (hmc_masked_kernels.hip).
-hipError_t launch_pass_masked(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s);
+hipError_t launch_pass_masked(const DevLattice& d, int colour, bool obs, int spt, int zc, double T,
+                              const SweepCarry& c, hipStream_t s);
 // The colour pass with the depth-two march (hmc_deep_kernels.hip).
-hipError_t launch_pass_deep(const DevLattice& d, int colour, bool obs, int spt, int zc, double T, hipStream_t s);
+hipError_t launch_pass_deep(const DevLattice& d, int colour, bool obs, int spt, int zc, double T,
+                            const SweepCarry& c, hipStream_t s);
 
 }  // namespace hmc
