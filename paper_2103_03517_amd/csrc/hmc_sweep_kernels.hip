@@ -447,11 +447,13 @@ void finalize_go(const DevLattice& d, const SweepPlan& p, int launch, bool obs, 
 }  // namespace
 
 // One launch pays while the work it repeats costs less than the launches it
-// saves.  Measured on MI355X, us per sampled sweep against the passes in their
-// best shape: FP32 16^3 6.2 for 12.7, 32^3 6.7 for 12.6, 64^3 9.1 for 14.2, 80^3
-// 12.5 for 17.7, 120 x 98 x 62 18.7 for 19.3 (unsampled 16.7 for 15.0), 112^3
-// 27.3 for 25.6; FP64 16^3 7.0 for 14.5, 48^3 9.3 for 15.4, 64^3 13.4 for 17.5,
-// 80^3 25.8 for 25.4.
+// saves.  Measured on MI355X, us per sampled sweep (in brackets unsampled) against
+// the passes in their default shape, each of which carries the finalize of the
+// sweep before: FP32 32^3 6.4 for 10.0 (5.8 for 8.2), 64^3 8.5 for 11.4 (7.8 for
+// 8.7), 84^3 12.4 for 14.4 (11.5 for 12.5); FP64 32^3 7.1 for 10.8 (6.6 for 9.6),
+// 60^3 12.6 for 13.1 (11.7 for 11.7), 66^3 14.4 for 16.3 (13.1 for 15.2).  Above
+// the line it lost already to passes with a finalize launch each: FP32 112^3 27.3
+// for 25.6, FP64 80^3 25.8 for 25.4.
 bool sweep_plan(const DevLattice& d, SweepPlan* plan)
 {
     constexpr int64_t kMost[2] = {600000, 300000};          // spins, FP32 and FP64
