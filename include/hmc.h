@@ -324,8 +324,8 @@ const char* hmc_last_error(const hmc_lattice* L);
  * Batches: many independent lattices (the separate runs at many
  * temperatures and sizes that Sec. 3 sweeps over, e.g. for m(T)) advanced
  * together.  A batch sweep issues one launch per colour pass for every
- * group of lattices that share a kernel variant (sites per thread and
- * halo width: at most 9 groups, usually one or two), and one finalize
+ * group of lattices that share a kernel variant (sites per thread and the
+ * geometry of a row: at most 9 groups, usually one or two), and one finalize
  * launch in which work-group i folds lattice i's counts and sums.  Each
  * lattice keeps its own spins, cone angle, sweep counter and
  * accumulators, and each of its tiles runs exactly as in hmc_sweep, so
