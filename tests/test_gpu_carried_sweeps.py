@@ -8,11 +8,12 @@ from tests import inputs
 pytestmark = pytest.mark.gpu
 
 # one record a pass or a few; about a wave's and a work-group's worth; a group
-# of 1024 and one plane more; the most a pass may leave (2048) and one plane more; rows of tiles and of two halo sites
+# of 1024 and one plane more; the most a pass may leave (2048) and one plane more;
+# rows of tiles and of two halo sites; FP64 with the most LDS a launch shape may take
 SHAPES = [((4, 2, 2), "periodic", (1, 2)), ((16, 16, 16), "antiperiodic", (4, 1)), ((32, 16, 63), "open", (1, 1)),
           ((32, 16, 65), "open", (1, 1)), ((32, 16, 257), "open", (1, 1)), ((64, 64, 128), "antiperiodic", (1, 1)),
           ((64, 64, 129), "open", (1, 1)), ((64, 64, 256), "periodic", (1, 1)), ((64, 64, 257), "open", (1, 1)),
-          ((1024, 6, 5), "open", (1, 2)), ((512, 4, 6), "periodic", (2, 3))]
+          ((1024, 6, 5), "open", (1, 2)), ((512, 4, 6), "periodic", (2, 3)), ((340, 4, 6), "periodic", (4, 2))]
 
 
 @pytest.fixture(scope="module")
