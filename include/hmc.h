@@ -395,7 +395,7 @@ int hmc_batch_reset_stats(hmc_batch* B);
  * first), the fastest admissible launch shape (sites_per_thread 1, 2, 4
  * within the LDS budget; z_chunk 2 .. 64, powers of two up to nz) with the
  * other sizes held; then the chunk size again.  trial_sweeps: 1 .. 1000.
- * The shapes are set on the lattices (hmc_get_launch reads them), the
+ * The shapes are set on the lattices, as hmc_set_launch sets them, the
  * chunk size on the batch (hmc_batch_get_chunk_bytes).  Every lattice's state is saved before and
  * restored after (host copies), so tuning leaves the chains where they
  * were.  Synchronises.  Errors: HMC_EINVAL, HMC_EHIP, HMC_ENOMEM (host). */

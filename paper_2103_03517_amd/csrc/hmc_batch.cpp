@@ -588,6 +588,7 @@ int hmc_batch_tune(hmc_batch* B, const double* T, int32_t trial_sweeps)
         for (size_t i : members) {
             B->lat[i]->batch_spt = B->lat[i]->spt = best.first;
             B->lat[i]->batch_zc = B->lat[i]->zc = best.second;
+            B->lat[i]->shape_set = true;
         }
     }
     // and the chunk size again with the final shapes

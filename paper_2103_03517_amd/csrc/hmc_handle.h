@@ -62,8 +62,8 @@ struct hmc_lattice {
     hipStream_t stream;
     hmc::Layout lay;
     int spt = 2, zc = 16;             // launch shape of the lattice's own sweeps
-    int batch_spt = 2, batch_zc = 16; // and in a batch; hmc_set_launch sets both
-    bool shape_set = false;           // by hmc_set_launch
+    int batch_spt = 2, batch_zc = 16; // and in a batch
+    bool shape_set = false;           // both by hmc_set_launch or hmc_batch_tune
     bool whole = false;               // a sweep is one launch (plan), unless a shape or a look-ahead is set
     hmc::SweepPlan plan;
     bool m_valid = false;
