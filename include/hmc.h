@@ -241,7 +241,8 @@ int hmc_set_state(hmc_lattice* L, const void* host_buf, size_t bytes);
  * FP32 and 32 at FP64 (16 with bond masks).  hmc_get_launch gives the shape
  * hmc_sweep uses; lattices of up to 600000 spins at FP32 (300000 at FP64) for
  * which neither a shape nor a look-ahead was set take a whole sweep per
- * launch instead, with the same spins.  In a batch, a lattice whose shape was not set takes a
+ * launch instead, except where their rows are so long that it would be slower,
+ * with the same spins.  In a batch, a lattice whose shape was not set takes a
  * default of its own: (1, 4), and (2, 8) for FP64 lattices above 64^3 spins.
  * Errors: HMC_EINVAL. */
 int hmc_set_launch(hmc_lattice* L, int32_t sites_per_thread, int32_t z_chunk);

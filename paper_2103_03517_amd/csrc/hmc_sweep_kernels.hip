@@ -41,9 +41,9 @@ template <typename R> struct TileCap;
 template <> struct TileCap<float> { static constexpr int threads = 512, black = 4096, red = 2304; };
 template <> struct TileCap<double> { static constexpr int threads = 256, black = 2048, red = 1280; };
 
-// Counts of the launch before that a thread of a tile sums: at most this many
-// times the work-group size tiles.
-constexpr int kCountLoads = 2;
+// Most tiles of a launch, two to a compute unit.  Every tile sums their counts,
+// a thread kMostTiles / work-group size of them.
+constexpr int kMostTiles = 512;
 
 // n / d for n * d < 2^32, d >= 2
 struct Div {
@@ -151,7 +151,8 @@ __global__ __launch_bounds__(TileCap<R>::threads) void sweep_kernel(const KArgs<
 {
     constexpr int NT = TileCap<R>::threads, SB = TileCap<R>::black, SR = TileCap<R>::red, NW = NT / 64;
     constexpr int NB = SB / NT, NR = (SR + NT - 1) / NT;      // black loads and red sites per thread
-    static_assert(SB % NT == 0, "black sites per thread");
+    constexpr int NC = kMostTiles / NT;                       // counts per thread
+    static_assert(SB % NT == 0 && kMostTiles % NT == 0, "black sites and counts per thread");
     __shared__ __align__(16) R smem[3 * (SB + SR)];
     __shared__ double tot[kObsRows];
     __shared__ unsigned long long totc;
@@ -172,9 +173,9 @@ __global__ __launch_bounds__(TileCap<R>::threads) void sweep_kernel(const KArgs<
     // the counts of the launch before, summed below: they move the angle one up or down
     // (added up only after the spins' loads have left; the first launch of a
     // call reads counts that nobody wrote and does not use them)
-    uint32_t cq[kCountLoads];
+    uint32_t cq[NC];
 #pragma unroll
-    for (int u = 0; u < kCountLoads; ++u)
+    for (int u = 0; u < NC; ++u)
         cq[u] = f.cnt[(size_t)prev * f.ntile + min(t + (uint32_t)u * NT, f.ntile - 1u)];
     // (through a buffer resource: as vector loads, which nothing waits for
     // before their use; scalar loads held up every load behind them)
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(TileCap<R>::threads) void sweep_kernel(const KArgs<
     {
         uint32_t c = 0;
 #pragma unroll
-        for (int u = 0; u < kCountLoads; ++u) c += t + (uint32_t)u * NT < f.ntile ? cq[u] : 0u;
+        for (int u = 0; u < NC; ++u) c += t + (uint32_t)u * NT < f.ntile ? cq[u] : 0u;
         c = wave_sum(c);                       // N < 2^32
         if (lane == 0) wacc[wave] = c;
     }
@@ -339,6 +340,7 @@ __global__ __launch_bounds__(TileCap<R>::threads) void sweep_kernel(const KArgs<
 struct Tiles {
     int ry = 0, zc = 0;
     uint32_t nyt = 0, n = 0;
+    double cost = 0.0;           // of a launch, cycles
     size_t bytes = 0;
 };
 
@@ -354,7 +356,6 @@ Tiles tiles_for(const DevLattice& d)
     using Cap = TileCap<R>;
     constexpr double kRed = sizeof(R) == 4 ? 550.0 : 1300.0, kBlack = sizeof(R) == 4 ? 700.0 : 1500.0, kRound = 7000.0;
     Tiles best;
-    double cost = 0.0;
     for (int r = 1; r <= kMaxTileEdge && r <= d.ny; ++r) {
         const int ry = (int)cdiv((uint64_t)d.ny, cdiv((uint64_t)d.ny, (uint64_t)r));       // equal tiles
         for (int p = 1; p <= kMaxTileEdge && p <= d.nz; ++p) {
@@ -365,8 +366,8 @@ Tiles tiles_for(const DevLattice& d)
             const double work = (ceil(red / 64) * kRed + ceil(black / 64) * kBlack) / 4;
             const double tiles = (double)((d.ny + ry - 1) / ry) * ((d.nz + zc - 1) / zc);
             const double c = ceil(tiles / 256) * work + ceil(tiles / 512) * kRound;
-            if (best.ry == 0 || c < cost) {
-                cost = c;
+            if (best.ry == 0 || c < best.cost) {
+                best.cost = c;
                 best.ry = ry;
                 best.zc = zc;
                 best.nyt = (uint32_t)((d.ny + ry - 1) / ry);
@@ -381,10 +382,13 @@ Tiles tiles_for(const DevLattice& d)
 template <typename R>
 bool plan_go(const DevLattice& d, SweepPlan* plan)
 {
+    constexpr double kPasses = sizeof(R) == 4 ? 10500.0 : 12000.0, kPassesSpin = sizeof(R) == 4 ? 0.0085 : 0.021;
     const Tiles tl = tiles_for<R>(d);
     const size_t spins = 6 * d.pitch;
     const size_t room = 16 * (size_t)d.Nc * sizeof(R);       // the constrained scratch: at least this
-    if (tl.n == 0 || tl.n > (uint32_t)(kCountLoads * TileCap<R>::threads) || spins + tl.bytes > room) return false;
+    if (tl.n == 0 || tl.n > (uint32_t)kMostTiles || tl.cost > kPasses + kPassesSpin * (double)d.N ||
+        spins + tl.bytes > room)
+        return false;
     plan->ry = tl.ry;
     plan->zc = tl.zc;
     plan->ntile = (int32_t)tl.n;
@@ -447,13 +451,21 @@ void finalize_go(const DevLattice& d, const SweepPlan& p, int launch, bool obs, 
 }  // namespace
 
 // One launch pays while the work it repeats costs less than the launches it
-// saves.  Measured on MI355X, us per sampled sweep (in brackets unsampled) against
-// the passes in their default shape, each of which carries the finalize of the
-// sweep before: FP32 32^3 6.4 for 10.0 (5.8 for 8.2), 64^3 8.5 for 11.4 (7.8 for
-// 8.7), 84^3 12.4 for 14.4 (11.5 for 12.5); FP64 32^3 7.1 for 10.8 (6.6 for 9.6),
-// 60^3 12.6 for 13.1 (11.7 for 11.7), 66^3 14.4 for 16.3 (13.1 for 15.2).  Above
-// the line it lost already to passes with a finalize launch each: FP32 112^3 27.3
-// for 25.6, FP64 80^3 25.8 for 25.4.
+// saves: up to a number of spins, and below it where the launch (tiles_for) costs
+// no more cycles than the passes in their default shape, kPasses + kPassesSpin a
+// spin.  Long rows leave room for tiles of a row or two only, which recompute
+// three to five red sites for one.  Measured on MI355X, us per sampled sweep (in
+// brackets unsampled) against those passes, each of which carries the finalize of
+// the sweep before: FP32 32^3 6.4 for 9.5 (5.8 for 7.8), 64^3 8.4 for 11.7 (7.7 for
+// 8.6), 84^3 12.1 for 14.5 (11.5 for 12.4); FP64 32^3 7.2 for 10.5 (6.6 for 9.5),
+// 66^3 14.1 for 16.6 (13.2 for 15.3).  Where the cost draws the line, kept: FP32
+// 128 x 128 x 32 12.6 for 14.8 (11.9 for 10.8), 320 x 16 x 16 8.1 for 11.1 (7.6
+// for 9.0); FP64 60^3 12.5 for 12.9 (11.7 for 11.6).  Left: FP32 272 x 32 x 64
+// 20.3 for 14.8 (19.0 for 12.9), 200 x 50 x 50 18.0 for 14.5 (17.0 for 10.7), 300 x 20
+// x 40 17.1 for 11.5 (15.7 for 9.2), 160 x 60 x 60 14.6 for 14.6 (13.7 for 12.6);
+// FP64 96 x 64 x 40 15.1 for 13.3 (13.9 for 12.0).  Above the spins' line it lost
+// already to passes with a finalize launch each: FP32 112^3 27.3 for 25.6, FP64 80^3
+// 25.8 for 25.4.
 bool sweep_plan(const DevLattice& d, SweepPlan* plan)
 {
     constexpr int64_t kMost[2] = {600000, 300000};          // spins, FP32 and FP64
