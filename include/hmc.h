@@ -243,7 +243,9 @@ int hmc_set_state(hmc_lattice* L, const void* host_buf, size_t bytes);
  * which neither a shape nor a look-ahead was set take a whole sweep per
  * launch instead, except where their rows are so long that it would be slower,
  * with the same spins.  In a batch, a lattice whose shape was not set takes a
- * default of its own: (1, 4), and (2, 8) for FP64 lattices above 64^3 spins.
+ * default of its own: at FP32 (1, 4), above 128^3 spins (1, 8) and above 14
+ * million (2, 16); at FP64 (1, 4), and above 64^3 spins (2, 8), (2, 16) where
+ * nx is 512 and (1, 8) where it is larger; above 256 MiB the default above.
  * Errors: HMC_EINVAL. */
 int hmc_set_launch(hmc_lattice* L, int32_t sites_per_thread, int32_t z_chunk);
 int hmc_get_launch(const hmc_lattice* L, int32_t* sites_per_thread, int32_t* z_chunk);

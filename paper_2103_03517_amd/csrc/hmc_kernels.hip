@@ -831,19 +831,35 @@ void default_shape(const DevLattice& d, int* spt, int* zc)
 
 // In a batch the other lattices fill the chip, so the slabs are as long as
 // re-reading their ends asks for, whatever the batch holds (a lattice's
-// result must not depend on its company).  Measured on MI355X, us per sampled
-// batch sweep: FP32, 24 lattices of 48^3 to 128^3: (1, 4) 148, (1, 8) 147, (1, 2)
-// 174, (2, 16) 182; 8 of 32^3 to 64^3: (1, 4) 22.5, (1, 8) 27.9, (2, 16) 62.  FP64, the same:
-// (2, 8) 387, (1, 8) 421, (1, 4) 466; 8 small ones: (1, 4) 30, (1, 8) 35, (2, 8) 51.
+// result must not depend on its company).  That is a compromise: long slabs leave
+// the chip idle where a batch is small, and in (2, 16) a batch that fills exactly
+// one round is hard to beat.  Measured on MI355X, us per sampled batch sweep in
+// (1, 4), (1, 8), (2, 8) and (2, 16).
+//   FP32: 4 x 64^3 21, 27, 38, 62; 24 of 48^3 to 128^3 162, 158, 172, 198; 8 x 128^3
+// 116, 113, 117, 109.  Above 128^3 the slabs' ends show: 4 x 160^3 116, 111, 115, 108;
+// 2 x 192^3 108, 101, 104, 102; 1 x 224^3 97, 86, 95, 88; 2 x 240^3 244, 231, 248, 262.
+// From 14 million spins on a lattice fills the chip alone: 256^3 130, 119, 118, 111.
+//   FP64: 4 x 64^3 29, 34, 49, 81 and 16 x 64^3 92, 82, 75, 94, but 32 x 64^3 165, 146,
+// 135, 127 (the line is the smaller batches'); 2 x 96^3 50, 45, 55, 90; 16 x 96^3 331, 303,
+// 268, 275; 8 x 160^3 756, 684, 591, 573.  Rows of 256 colour sites, where the halo
+// of a window is as large as the window: 2 x 512 x 128 x 64 179, 153, 172, 160 and 6 x
+// 512 x 64 x 64 323, 296, 291, 278.  Longer ones, in tiles: 4 x 600 x 128 x 64 478, 429, 466,
+// 452; 8 x 640 x 64 x 32 202, 178, 203, 226; 1024 x 256 x 32 172, 147 (two sites refused).
 void default_batch_shape(const DevLattice& d, int* spt, int* zc)
 {
     if ((uint64_t)d.N * 3ull * (uint64_t)(d.precision / 8) > kDeepMarchBytes) {
         default_shape(d, spt, zc);
         return;
     }
-    const bool two = d.precision == 64 && d.N > (int64_t)64 * 64 * 64 && pass_shape_ok(64, d.hx, 2);
-    *spt = two ? 2 : 1;
-    *zc = two ? 8 : 4;
+    if (d.precision == 32) {
+        const bool large = d.N > 14000000;
+        *spt = large ? 2 : 1;
+        *zc = large ? 16 : (d.N > (int64_t)128 * 128 * 128 ? 8 : 4);
+    } else {
+        const bool small = d.N <= (int64_t)64 * 64 * 64, tiles = geometry_of(d.hx) == 0;
+        *spt = small || tiles ? 1 : 2;
+        *zc = small ? 4 : (d.hx < kThreads || tiles ? 8 : 16);
+    }
 }
 
 // Colour-split bond masks from masks in site order: site i = 2k + p of row
