@@ -739,7 +739,7 @@ static_assert(offsetof(PassSlot, theta) == offsetof(DevState, theta) && offsetof
 
 struct PassHead {
     const PassSlot* from;    // what the sweep (red: the one before) left, or the chain state
-    PassSlot* to;            // red of a carried sweep: what it leaves; else null
+    PassSlot* to;            // red: what it leaves; else null
     const uint32_t* red;     // the counts of the sweep before
     const uint32_t* black;
     uint32_t nrec;           // of each: 0 where the pass takes the cone angle as it is
@@ -747,8 +747,12 @@ struct PassHead {
     double T, N;
 };
 
-// The head of a pass: cone angle and sweep number, from vector loads, which hold
-// up nothing before their use.  load() comes before the loads of the march's
+// The head of a pass of a carried sweep: cone angle and sweep number, from vector
+// loads, which hold up nothing before their use.  (Other passes take them by scalar
+// loads at their start.  Through this head, whose table look-up waits behind the
+// first planes' loads, they took 0.3 to 4 % longer: MI355X, us a sampled sweep, 464^3
+// FP32 750.5 for 747.3, 2 x 2 x 100000 FP64 632 for 608, one sweep a call of 128^3 FP32
+// 26.8 for 25.8, FP64 45.6 for 44.1.)  load() comes before the loads of the march's
 // first planes, table() after them, ready() stands for the barrier that follows.
 template <typename R, int C>
 struct HeadLoads {
@@ -1227,8 +1231,8 @@ __device__ __forceinline__ void march2(const KArgs<R>& a, const Arrays<R>& g, co
 
 // One work-group of a colour pass: logical tile b (in-plane window or tile
 // b % n, of z-slab b / n) of the lattice described by a, with the march of
-// depth two when DEEP.  head: null in a batch, whose passes read the chain
-// state; wtot: a word per wave in shared memory with it.
+// depth two when DEEP.  head: of a carried sweep, else null (the pass reads the
+// chain state); wtot: a word per wave in shared memory with it.
 template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, bool DEEP>
 __device__ __forceinline__ void pass_tile(const KArgs<R>& a, const PassGeom& q, const uint32_t zc, const uint32_t b,
                                           const R scale, unsigned char* smem, const PassHead* head, uint32_t* wtot)
@@ -1340,7 +1344,7 @@ __device__ __forceinline__ void pass_tile(const KArgs<R>& a, const PassGeom& q, 
     };
     if constexpr (DEEP) march2<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc, table, ready);
     else march1<R, C, OBS, SPT, GEO, MASK>(a, g, x, nacc, acc, table, ready);
-    if (C == 0 && head && head->to && b == 0 && threadIdx.x == 0)
+    if (C == 0 && head && b == 0 && threadIdx.x == 0)
         *head->to = PassSlot{hl.theta, 0u, (int64_t)hl.sweep};
     // LDS is free after the last barrier of the march
     block_end<R, OBS, false>(a, C, b, nacc, acc, reinterpret_cast<double*>(smem));
@@ -1356,8 +1360,17 @@ constexpr int pass_waves_per_eu()
 
 template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, bool DEEP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, SPT, DEEP>())))
-void pass_kernel(const KArgs<R> a, const PassGeom q, const uint32_t zc, const uint32_t nblk, const R scale,
-                 const PassHead h)
+void pass_kernel(const KArgs<R> a, const PassGeom q, const uint32_t zc, const uint32_t nblk, const R scale)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    pass_tile<R, C, OBS, SPT, GEO, MASK, DEEP>(a, q, zc, xcd_remap(blockIdx.x, nblk), scale, smem, nullptr, nullptr);
+}
+
+// A pass of a carried sweep.
+template <typename R, int C, bool OBS, int SPT, int GEO, bool MASK, bool DEEP>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(pass_waves_per_eu<R, SPT, DEEP>())))
+void carried_pass_kernel(const KArgs<R> a, const PassGeom q, const uint32_t zc, const uint32_t nblk, const R scale,
+                         const PassHead h)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t wtot[kThreads / 64];
@@ -1384,26 +1397,32 @@ struct PassLaunch {
     static void go(const KArgs<R>& args, const DevLattice& d, int zc, double T, const SweepCarry& c, hipStream_t s)
     {
         const uint32_t nblk = (uint32_t)pass_blocks(d, SPT, zc);
+        const PassGeom& q = pass_geom(d, SPT);
+        const size_t lds = pass_lds_bytes(d, SPT);
+        const R scale = Prim<R>::scale_for(T);
+        if (!c.on) {
+            pass_kernel<R, C, OBS, SPT, GEO, MASK, DEEP><<<nblk, kThreads, lds, s>>>(args, q, (uint32_t)zc, nblk, scale);
+            return;
+        }
         KArgs<R> a = args;
-        PassSlot* slot = c.on ? carry_slots(d) : nullptr;
-        const bool head = c.on && C == 0 && c.sweep > 0;         // finalizes the sweep before
+        PassSlot* slot = carry_slots(d);
+        const bool head = C == 0 && c.sweep > 0;                 // finalizes the sweep before
         PassHead h{};
         h.from = reinterpret_cast<const PassSlot*>(d.st);
         if (head) h.from = slot + ((c.sweep - 1) & 1);
-        else if (c.on && C == 1) h.from = slot + (c.sweep & 1);
+        else if (C == 1) h.from = slot + (c.sweep & 1);
         h.red = red_counts(d, c.sweep - 1);
         h.black = d.cnt + d.max_blocks;
         h.nrec = head ? nblk : 0u;
         h.fin = c.fin;
         h.T = T;
         h.N = (double)d.N;
-        if (c.on && C == 0) {
+        if (C == 0) {
             h.to = slot + (c.sweep & 1);
             a.cnt = red_counts(d, c.sweep);
         }
         const uint32_t grid = nblk + (head ? 1u : 0u);
-        pass_kernel<R, C, OBS, SPT, GEO, MASK, DEEP><<<grid, kThreads, pass_lds_bytes(d, SPT), s>>>(
-            a, pass_geom(d, SPT), (uint32_t)zc, nblk, Prim<R>::scale_for(T), h);
+        carried_pass_kernel<R, C, OBS, SPT, GEO, MASK, DEEP><<<grid, kThreads, lds, s>>>(a, q, (uint32_t)zc, nblk, scale, h);
     }
 
     template <typename R, int SPT, int GEO>
