@@ -1048,10 +1048,15 @@ hipError_t launch_plane_means(const DevLattice& d, double* out, hipStream_t s)
 // Planes per thread of the measurement: the shortest slabs that give 512
 // work-groups at most, which shares the work-group sums where the chip is not
 // filled anyway; above eight planes the shortest that give 2048 (eight to a
-// compute unit).  The rule depends on the lattice alone: hmc_measure_static and
-// a batch measure with the same grid, so with the same bits.
+// compute unit).  Planes of a few sites take one plane a thread: columns shorter
+// than a 32-byte sector would scatter a wave's loads over as many lines as it has
+// slabs (MI355X, us per hmc_observables in slabs and so: 2 x 2 x 4000000 FP32 383,
+// 119, FP64 380, 158; 2 x 6 x 700000 FP32 87, 77; at the line 4 x 4 x 1000000 FP32 98,
+// 120, 2 x 4 x 1000000 FP64 88, 89).  The rule depends on the lattice alone:
+// hmc_measure_static and a batch measure with the same grid, so with the same bits.
 int measure_planes(const DevLattice& d)
 {
+    if (d.P * (d.precision / 8) < 32) return 1;
     auto planes = [&](uint64_t blocks) {
         const uint64_t slabs = blocks * kThreads / (uint64_t)d.P;
         return slabs == 0 ? d.nz : (int)cdiv((uint64_t)d.nz, slabs);
