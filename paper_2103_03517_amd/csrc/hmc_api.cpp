@@ -346,7 +346,7 @@ int hmc_sweep(hmc_lattice* L, double T, int32_t n_sweeps, int32_t sample)
     const bool obs = sample != 0;
     // small lattices: a launch per sweep, unless a launch shape or a look-ahead
     // of the passes was set
-    if (L->whole && !L->shape_set && L->d.prefetch == 0) {
+    if (L->whole && L->plan.pays[obs] && !L->shape_set && L->d.prefetch == 0) {
         if (n_sweeps == 0) return HMC_OK;
         int st = HMC_OK;
         const int32_t odd = n_sweeps & 1;

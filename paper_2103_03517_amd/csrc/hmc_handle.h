@@ -64,7 +64,7 @@ struct hmc_lattice {
     int spt = 2, zc = 16;             // launch shape of the lattice's own sweeps
     int batch_spt = 2, batch_zc = 16; // and in a batch
     bool shape_set = false;           // both by hmc_set_launch or hmc_batch_tune
-    bool whole = false;               // a sweep is one launch (plan), unless a shape or a look-ahead is set
+    bool whole = false;               // a sweep is one launch (plan) where it pays, unless a shape or a look-ahead is set
     hmc::SweepPlan plan;
     bool m_valid = false;
     char err[256] = {0};

@@ -164,6 +164,7 @@ hipError_t launch_finalize(const DevLattice& d, int64_t red_blocks, int64_t blac
 struct SweepPlan {
     int32_t ry = 0, zc = 0;      // rows and planes of a tile
     int32_t ntile = 0;
+    bool pays[2] = {false, false};   // an unsampled, a sampled sweep in one launch costs no more than its passes
 };
 bool sweep_plan(const DevLattice& d, SweepPlan* plan);
 hipError_t launch_sweep_copy(const DevLattice& d, hipStream_t s);

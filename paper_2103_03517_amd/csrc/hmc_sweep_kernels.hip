@@ -369,7 +369,7 @@ Parts parts_of(uint32_t n)
 }
 
 // (The divisions stand outside the double loop: inside it they took a new lattice
-// 2 to 3 us of the host's time.)
+// 1 us of the host's time.)
 template <typename R>
 Tiles tiles_for(const DevLattice& d)
 {
@@ -403,13 +403,14 @@ Tiles tiles_for(const DevLattice& d)
 template <typename R>
 bool plan_go(const DevLattice& d, SweepPlan* plan)
 {
-    constexpr double kPasses = sizeof(R) == 4 ? 10500.0 : 12000.0, kPassesSpin = sizeof(R) == 4 ? 0.0085 : 0.021;
+    // cycles of the passes of a sweep: unsampled, sampled; of a launch and per spin
+    constexpr double kPasses[2] = {sizeof(R) == 4 ? 10500.0 : 12000.0, sizeof(R) == 4 ? 11800.0 : 12000.0};
+    constexpr double kPassesSpin[2] = {sizeof(R) == 4 ? 0.0085 : 0.021, sizeof(R) == 4 ? 0.0095 : 0.021};
     const Tiles tl = tiles_for<R>(d);
     const size_t spins = 6 * d.pitch;
     const size_t room = 16 * (size_t)d.Nc * sizeof(R);       // the constrained scratch: at least this
-    if (tl.n == 0 || tl.n > (uint32_t)kMostTiles || tl.cost > kPasses + kPassesSpin * (double)d.N ||
-        spins + tl.bytes > room)
-        return false;
+    if (tl.n == 0 || tl.n > (uint32_t)kMostTiles || spins + tl.bytes > room) return false;
+    for (int obs = 0; obs < 2; ++obs) plan->pays[obs] = tl.cost <= kPasses[obs] + kPassesSpin[obs] * (double)d.N;
     plan->ry = tl.ry;
     plan->zc = tl.zc;
     plan->ntile = (int32_t)tl.n;
@@ -473,20 +474,21 @@ void finalize_go(const DevLattice& d, const SweepPlan& p, int launch, bool obs, 
 
 // One launch pays while the work it repeats costs less than the launches it
 // saves: up to a number of spins, and below it where the launch (tiles_for) costs
-// no more cycles than the passes in their default shape, kPasses + kPassesSpin a
-// spin.  Long rows leave room for tiles of a row or two only, which recompute
-// three to five red sites for one.  Measured on MI355X, us per sampled sweep (in
+// no more cycles than the passes in their default shape.  Long rows leave room for
+// tiles of a row or two only, which recompute three to five red sites for one.
+// The lines of sampled and unsampled sweeps differ (an unsampled sweep sums
+// integers only, so it leaves the same state either way; sampled ones keep to one
+// form, for the order of their sums).  Measured on MI355X, us per sampled sweep (in
 // brackets unsampled) against those passes, each of which carries the finalize of
 // the sweep before: FP32 32^3 6.4 for 9.5 (5.8 for 7.8), 64^3 8.4 for 11.7 (7.7 for
 // 8.6), 84^3 12.1 for 14.5 (11.5 for 12.4); FP64 32^3 7.2 for 10.5 (6.6 for 9.5),
-// 66^3 14.1 for 16.6 (13.2 for 15.3).  Where the cost draws the line, kept: FP32
-// 128 x 128 x 32 12.6 for 14.8 (11.9 for 10.8), 320 x 16 x 16 8.1 for 11.1 (7.6
-// for 9.0); FP64 60^3 12.5 for 12.9 (11.7 for 11.6).  Left: FP32 272 x 32 x 64
-// 20.3 for 14.8 (19.0 for 12.9), 200 x 50 x 50 18.0 for 14.5 (17.0 for 10.7), 300 x 20
-// x 40 17.1 for 11.5 (15.7 for 9.2), 160 x 60 x 60 14.6 for 14.6 (13.7 for 12.6);
-// FP64 96 x 64 x 40 15.1 for 13.3 (13.9 for 12.0).  Above the spins' line it lost
-// already to passes with a finalize launch each: FP32 112^3 27.3 for 25.6, FP64 80^3
-// 25.8 for 25.4.
+// 66^3 14.1 for 16.6 (13.1 for 15.2).  Where the cost draws the line: FP32 128 x 128
+// x 32 12.6 for 14.8 (11.9 for 10.8); sampled only 256 x 32 x 32 11.2 for 12.2 (10.4 for
+// 9.3), 128 x 68 x 68 13.8 for 14.4 (12.8 for 12.4); passes 160 x 60 x 60 14.6 for 14.6
+// (13.7 for 12.6), 200 x 50 x 50 18.0 for 14.5 (17.0 for 10.7), 272 x 32 x 64 20.3 for
+// 14.8 (19.0 for 12.9); FP64 60^3 12.5 for 12.9 (11.7 for 11.6), passes 96 x 64 x 40 15.1
+// for 13.3 (13.9 for 12.0).  Above the spins' line it lost already to passes with a
+// finalize launch each: FP32 112^3 27.3 for 25.6, FP64 80^3 25.8 for 25.4.
 bool sweep_plan(const DevLattice& d, SweepPlan* plan)
 {
     constexpr int64_t kMost[2] = {600000, 300000};          // spins, FP32 and FP64

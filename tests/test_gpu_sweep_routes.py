@@ -22,7 +22,10 @@ PASSES = [((272, 32, 64), "periodic", (32,)), ((320, 32, 32), "open", (32,)), ((
           ((200, 50, 50), "antiperiodic", (32,)), ((256, 256, 8), "periodic", (32,)), ((96, 64, 40), "periodic", (64,)),
           ((92, 82, 80), "periodic", (32,)), ((68, 68, 66), "periodic", (64,)), ((1024, 2, 4), "periodic", (32, 64)),
           ((4, 2, 2), "periodic", (32, 64)), ((2, 16, 16), "periodic", (32, 64)), ((16, 16, 1), "open", (32, 64))]
-CASES = [(s, b, p, True) for s, b, ps in WHOLE for p in ps] + [(s, b, p, False) for s, b, ps in PASSES for p in ps]
+# sampled sweeps whole, unsampled ones in passes
+SAMPLED = [((256, 32, 32), "open", (32,)), ((128, 68, 68), "antiperiodic", (32,))]
+CASES = [(s, b, p, w) for cases, w in ((WHOLE, (True, True)), (PASSES, (False, False)), (SAMPLED, (False, True)))
+         for s, b, ps in cases for p in ps]
 
 
 @pytest.fixture(scope="module")
@@ -48,7 +51,7 @@ def test_route_and_result(H, shape, boundary, precision, whole, masked):
     for n, smp in ((3, False), (4, True), (1, True)):
         one.set_timing(True)
         one.sweep(0.9, n, sample=smp)
-        assert one.read_timing()["pass"]["count"] == (n if whole else 2 * n)
+        assert one.read_timing()["pass"]["count"] == (n if whole[smp] else 2 * n)
         one.set_timing(False)
         for part in [1] * n:
             split.sweep(0.9, part, sample=smp)
