@@ -164,6 +164,8 @@ int refresh_table(hmc_batch* B)
         same = B->shape[i] == std::make_pair(B->lat[i]->batch_spt, B->lat[i]->batch_zc);
     if (same) return HMC_OK;
 
+    // (from here on a failure leaves shapes and launches that the device has not got)
+    B->table_valid = false;
     hipError_t e = staging_wait(B);
     if (e != hipSuccess) return bfail(B, HMC_EHIP, "waiting for the staging buffer", e);
     char* tab = B->staging + B->lay.off_tab;
