@@ -1474,8 +1474,8 @@ struct PassLaunch {
 // The bytes ask for one read of the spins; what a one-site-per-thread launch
 // spent its time on is the work-group sum of ten doubles, about as many
 // instructions as the 64 sites of a wave.  A slab shares that sum between its
-// planes (measured on MI355X with its finalize against one site per thread:
-// 256^3 FP32 57 us for 116, 464^3 330 for 686, 256^3 FP64 116 for 144).
+// planes (us per hmc_observables on MI355X against one site per thread: 256^3
+// FP32 67 for 119, 464^3 332 for 685, 256^3 FP64 125 for 157).
 // Every term is formed in the spin precision and added in FP64.
 // ---------------------------------------------------------------------------
 template <typename R>
